@@ -75,7 +75,8 @@ int32_t check_no_overlap(std::initializer_list<Range> outs, std::initializer_lis
 }
 
 // The forward kernel for a set of outputs: values only (one lane per point)
-// unless dY is stored or the backward is fused (four lanes per point).
+// unless dY is stored or the backward is fused (four lanes per point); past
+// the compile-time degrees one lane per (point, order).
 // variant: see sph::FwdVariant (fn == nullptr where it does not exist).
 sph::KernelInfo fwd_info(int32_t dtype, int L, int norm, bool store_dy, bool fused,
                          int variant = sph::kVarDefault) {
@@ -89,6 +90,8 @@ sph::KernelInfo fwd_info(int32_t dtype, int L, int norm, bool store_dy, bool fus
        {sph::fwd_derivs_f64_n1_m0, sph::fwd_derivs_f64_n1_m1, sph::fwd_derivs_f64_n1_m2}}};
   const int d = dtype == SPH_F64 ? 1 : 0;
   const int n = norm ? 1 : 0;
+  if (variant == sph::kVarDefault && L > (d ? sph::kCompileMax<double> : sph::kCompileMax<float>))
+    return d ? sph::ord_info_f64(L, n, true, store_dy, fused) : sph::ord_info_f32(L, n, true, store_dy, fused);
   if (!store_dy && !fused) return kValues[d][n](L, variant);
   const int mode = !fused ? sph::kDerivStore : (store_dy ? sph::kDerivFusedStore : sph::kDerivFused);
   return kDerivs[d][n][mode](L, variant);
@@ -285,6 +288,7 @@ Choice autotune(int32_t dtype, int L, int norm, bool store_dy, bool fused, sph::
     for (int bpc : kBpcCandidates) {
       const unsigned grid = batched_grid(ki, params.n, bpc);
       sph::FwdParams p = params;
+      p.tile = ki.tile_points;
       if (launch(ki.fn, grid, ki.block, lds, &p, s) != hipSuccess) continue;  // warm-up
       (void)hipEventRecord(e0, s);
       constexpr int reps = 3;
@@ -348,7 +352,7 @@ int32_t sph_compute_with_gradients(const void* xyz, int64_t n, int32_t l_max, in
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
-  sph::FwdParams p{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr};
+  sph::FwdParams p{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr, ki.tile_points};
   const int64_t grid = plain_grid(ceil_div(n, ki.tile_points));
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, ki.lds_bytes, &p,
              static_cast<hipStream_t>(stream));
@@ -441,7 +445,7 @@ int32_t sph_compute_with_hessians(const void* xyz, int64_t n, int32_t l_max, int
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
   hipStream_t s = static_cast<hipStream_t>(stream);
   // values and first derivatives: the forward kernel of sph_compute_with_gradients
-  sph::FwdParams pf{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr};
+  sph::FwdParams pf{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr, kf.tile_points};
   e = launch(kf.fn, static_cast<unsigned>(plain_grid(ceil_div(n, kf.tile_points))), kf.block, kf.lds_bytes, &pf, s);
   if (e != hipSuccess) return device_fail(e, "forward launch");
   sph::HessParams ph{xyz, n, l_max, d2Y};
@@ -674,6 +678,7 @@ int32_t sph_batched_compute(const void* xyz, const int64_t* offsets, int64_t n_e
   e = ensure_lds(ki.fn, lds);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
   const unsigned grid = batched_grid(ki, n_points, ch.blocks_per_cu);
+  p.tile = ki.tile_points;
 
   if (!g_use_graph || capturing) {
     e = launch(ki.fn, grid, ki.block, lds, &p, s);

@@ -25,15 +25,21 @@ bool in_range(int L) { return L >= 0 && L <= kMaxL; }
 constexpr bool kNorm = SPH_NORM != 0;
 // l_max <= 12 (float) and l_max <= 8 (double) are specialised at compile
 // time (degree loops unrolled, coefficients as literals, order-m terms
-// tabulated); larger l_max use the run-time-degree kernel of the smallest
-// m-extent bucket that covers l_max.
-constexpr int kSpecMax = std::is_same_v<T, float> ? 12 : 8;
+// tabulated).  The run-time-degree kernels, of the smallest m-extent bucket
+// that covers l_max, are variants; past kSpecMax the default is k_ord, whose
+// tables are elsewhere.
+constexpr int kSpecMax = kCompileMax<T>;
 constexpr int kSpecSlots = kSpecMax + 1 > 0 ? kSpecMax + 1 : 1;
 
 #if SPH_FAMILY == 1
+// Values only: the run-time-degree kernel is a variant of the compile-time
+// degrees alone, so no wider bucket than theirs is needed.
 template <int MM, int LT>
 const void* kernel_ptr() {
-  return reinterpret_cast<const void*>(&k_fwd<T, MM, LT, kNorm>);
+  if constexpr (MM > kBuckets[bucket_index(kSpecMax)])
+    return nullptr;
+  else
+    return reinterpret_cast<const void*>(&k_fwd<T, MM, LT, kNorm>);
 }
 template <int LT>
 const void* alt_ptr() {
@@ -73,10 +79,10 @@ const void* split_ptr() {
     return nullptr;
 }
 // The run-time-degree kernel with each group's degrees split between two
-// waves (no fused backward).
+// waves (no fused backward; l_max past the compile-time kernels).
 template <int MM>
 const void* split_rt_ptr() {
-  if constexpr (!kFused)
+  if constexpr (!kFused && MM > kSpecMax)
     return reinterpret_cast<const void*>(&k_fwd4<T, MM, -1, kNorm, kFused, kStore, 1, 2>);
   else
     return nullptr;
@@ -201,14 +207,9 @@ const void* pick(int L, int variant, int& nw, int& ds, bool quad) {
         ds = 2;
         return tables().spec_split[L];
       }
-      // run-time degrees: the split groups measured 27-34 % faster (float
-      // l_max 16 and 32, double 16); the fused backward has no split form
-      if (!ct && quad && tables().buckets_split[bucket_index(L)] != nullptr) {
-        ds = 2;
-        return tables().buckets_split[bucket_index(L)];
-      }
-      if (ct && quad) nw = quad_waves<T>(L);
-      return ct ? tables().spec[L] : tables().buckets[bucket_index(L)];
+      if (!ct) return nullptr;  // k_ord, see ord_info
+      if (quad) nw = quad_waves<T>(L);
+      return tables().spec[L];
     case kVarTile16:
       return ct ? tables().spec_alt[L] : nullptr;
     case kVarRuntime:  // the unsplit run-time-degree kernel

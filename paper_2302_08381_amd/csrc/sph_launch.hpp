@@ -24,7 +24,12 @@ struct FwdParams {
   const int64_t* offsets; // CSR offsets or null (no validation)
   int64_t n_env;
   int32_t* status;        // device status word or null
+  int32_t tile = 0;       // points per tile (k_ord)
 };
+
+// Largest l_max of the compile-time forward kernels; k_ord serves the rest.
+template <typename T>
+inline constexpr int kCompileMax = sizeof(T) == 4 ? 12 : 8;
 
 struct BwdParams {
   const void* dY;
@@ -152,9 +157,8 @@ struct KernelInfo {
 //                (unrolled) kernel where one exists, on its
 //                default tile (32 points on two waves for float l_max <= 8,
 //                the degree-split tile where that measured faster, else 16
-//                points on one wave), else the run-time-degree kernel (with
-//                each group's degrees split between two waves unless the
-//                backward is fused)
+//                points on one wave); past them k_ord (not in these tables,
+//                see ord_info)
 //   kVarTile16   the compile-time kernel on an unsplit 16-point, one-wave tile
 //   kVarRuntime  the unsplit run-time-degree (not unrolled) kernel
 //   kVarSplit    a degree-split kernel: the compile-time one (float l_max
@@ -179,6 +183,10 @@ KernelInfo fwd_derivs_f64_n0_m2(int L, int variant);
 KernelInfo fwd_derivs_f64_n1_m0(int L, int variant);
 KernelInfo fwd_derivs_f64_n1_m1(int L, int variant);
 KernelInfo fwd_derivs_f64_n1_m2(int L, int variant);
+// l_max past the compile-time kernels (kCompileMax): k_ord for the outputs
+// asked for, tile_points points per block (the launch sets FwdParams::tile).
+KernelInfo ord_info_f32(int L, int normalize, bool store_y, bool store_dy, bool bwd);
+KernelInfo ord_info_f64(int L, int normalize, bool store_y, bool store_dy, bool bwd);
 KernelInfo bwd_info_f32(int L);
 KernelInfo bwd_info_f64(int L);
 KernelInfo dbwd_info_f32(int L, int normalize);
