@@ -121,6 +121,19 @@ int32_t sph_backward(const void* dY, const void* grad_Y, int64_t n, int32_t l_ma
                      int32_t dtype, void* grad_xyz, void* stream);
 
 /*
+ * sph_vector_jacobian -- the same product from the points instead of stored
+ * derivatives: grad_xyz[i,a] = sum_k grad_Y[i,k] * dY_k/dx_a(xyz[i]), with
+ * the derivatives of Eq. iter-deri (normalize = 1: and the chain rule through
+ * x/r) formed in registers.  A forward that is only differentiated needs no
+ * dY, neither written nor read back.
+ *   xyz        in  [n,3]
+ *   grad_Y     in  [n,K]
+ *   grad_xyz   out [n,3]
+ */
+int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int32_t l_max,
+                            int32_t normalize, int32_t dtype, void* grad_xyz, void* stream);
+
+/*
  * sph_double_backward -- the derivatives of L' = sum_{i,a} v[i,a] grad_xyz[i,a]
  * where grad_xyz is the output of sph_backward:
  *   grad_grad_Y[i,k] = sum_a v[i,a] dY[i,a,k]

@@ -32,6 +32,7 @@ from ._native import (  # noqa: F401
     sph_e3nn_coordinates,
     sph_radial_expansion,
     sph_radial_expansion_backward,
+    sph_vector_jacobian,
     version,
 )
 from .autograd import (  # noqa: F401

@@ -44,6 +44,7 @@ _SIGNATURES = {
     "sph_compute_with_gradients": (_i32, [_vp, _i64, _i32, _i32, _i32, _vp, _vp, _vp]),
     "sph_compute_with_hessians": (_i32, [_vp, _i64, _i32, _i32, _i32, _vp, _vp, _vp, _vp]),
     "sph_backward": (_i32, [_vp, _vp, _i64, _i32, _i32, _vp, _vp]),
+    "sph_vector_jacobian": (_i32, [_vp, _vp, _i64, _i32, _i32, _i32, _vp, _vp]),
     "sph_double_backward": (_i32, [_vp, _vp, _vp, _i64, _i32, _i32, _i32, _vp, _vp, _vp]),
     "sph_batched_compute": (_i32, [_vp, _vp, _i64, _i64, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp]),
     "sph_radial_expansion": (_i32, [_vp, _vp, _i64, _i64, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp]),
@@ -277,6 +278,24 @@ def sph_backward(dY: torch.Tensor, grad_Y: torch.Tensor, l_max: int, grad_xyz: t
     with torch.cuda.device(dY.device):
         _check(lib().sph_backward(_ptr(dY), _ptr(grad_Y), n, int(l_max), _dtype_code(dY), _ptr(grad_xyz),
                                   _stream(dY.device)))
+    return grad_xyz
+
+
+def sph_vector_jacobian(xyz: torch.Tensor, grad_Y: torch.Tensor, l_max: int, normalize: bool = True,
+                        grad_xyz: torch.Tensor | None = None):
+    """grad_xyz[n,3] = sum_k grad_Y[n,k] dY_k/dxyz at the points, without stored
+    derivatives (include/sph.h: sph_vector_jacobian)."""
+    _check_xyz(xyz)
+    n = xyz.shape[0]
+    K = (int(l_max) + 1) ** 2
+    _need(grad_Y, "grad_Y", (n, K), xyz.dtype, xyz.device)
+    if grad_xyz is None:
+        grad_xyz = torch.empty((n, 3), dtype=xyz.dtype, device=xyz.device)
+    else:
+        _need(grad_xyz, "grad_xyz", (n, 3), xyz.dtype, xyz.device)
+    with torch.cuda.device(xyz.device):
+        _check(lib().sph_vector_jacobian(_ptr(xyz), _ptr(grad_Y), n, int(l_max), int(bool(normalize)),
+                                         _dtype_code(xyz), _ptr(grad_xyz), _stream(xyz.device)))
     return grad_xyz
 
 

@@ -1,12 +1,12 @@
 """torch.autograd wrapper with first and second derivatives.
 
-Forward: Y = sph(xyz).  When xyz needs a gradient the forward also stores
-dY (one pass, sph_compute_with_gradients) and the backward contracts it with
-the upstream gradient (sph_backward), as the paper's PyTorch binding does
-with the derivatives of the forward pass (Sec. III).  That backward is itself
-a differentiable function of (grad_Y, xyz) whose derivatives come from
-sph_double_backward, so forces trained through an energy (double backward)
-work.  All arithmetic runs in the HIP kernels.
+Forward: Y = sph(xyz), values only.  The backward forms the derivatives again
+from the points, in registers, and contracts them with the upstream gradient
+(sph_vector_jacobian): storing dY in the forward and reading it back would
+move seven times the bytes.  That backward is itself a differentiable
+function of (grad_Y, xyz) whose derivatives come from sph_double_backward, so
+forces trained through an energy (double backward) work.  All arithmetic runs
+in the HIP kernels.
 """
 from __future__ import annotations
 
@@ -17,11 +17,11 @@ from . import _native
 
 class _SphBackward(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, grad_Y, xyz, dY, l_max, normalize):
+    def forward(ctx, grad_Y, xyz, l_max, normalize):
         ctx.save_for_backward(grad_Y, xyz)
         ctx.l_max = l_max
         ctx.normalize = normalize
-        return _native.sph_backward(dY, grad_Y.contiguous(), l_max)
+        return _native.sph_vector_jacobian(xyz, grad_Y.contiguous(), l_max, normalize)
 
     @staticmethod
     def backward(ctx, v):
@@ -29,10 +29,10 @@ class _SphBackward(torch.autograd.Function):
         want_gg = ctx.needs_input_grad[0]
         want_x = ctx.needs_input_grad[1]
         if not (want_gg or want_x):
-            return None, None, None, None, None
+            return None, None, None, None
         ggY, g2 = _native.sph_double_backward(xyz, grad_Y.contiguous(), v.contiguous(), ctx.l_max,
                                               ctx.normalize, want_grad_grad_Y=want_gg, want_grad_xyz=want_x)
-        return ggY, g2, None, None, None
+        return ggY, g2, None, None
 
 
 class _Sph(torch.autograd.Function):
@@ -40,21 +40,13 @@ class _Sph(torch.autograd.Function):
     def forward(ctx, xyz, l_max, normalize):
         ctx.l_max = l_max
         ctx.normalize = normalize
-        if xyz.requires_grad:
-            Y, dY = _native.sph_compute_with_gradients(xyz, l_max, normalize)
-            ctx.save_for_backward(xyz, dY)
-        else:
-            Y = _native.sph_compute(xyz, l_max, normalize)
-            ctx.save_for_backward(xyz, None)
-        return Y
+        ctx.save_for_backward(xyz)
+        return _native.sph_compute(xyz, l_max, normalize)
 
     @staticmethod
     def backward(ctx, grad_Y):
-        xyz, dY = ctx.saved_tensors
-        if dY is None:
-            _, dY = _native.sph_compute_with_gradients(xyz.detach(), ctx.l_max, ctx.normalize)
-        gx = _SphBackward.apply(grad_Y, xyz, dY, ctx.l_max, ctx.normalize)
-        return gx, None, None
+        (xyz,) = ctx.saved_tensors
+        return _SphBackward.apply(grad_Y, xyz, ctx.l_max, ctx.normalize), None, None
 
 
 def spherical_harmonics(xyz: torch.Tensor, l_max: int, normalize: bool = True) -> torch.Tensor:

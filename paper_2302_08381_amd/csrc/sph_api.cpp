@@ -99,6 +99,9 @@ sph::KernelInfo fwd_info(int32_t dtype, int L, int norm, bool store_dy, bool fus
 sph::KernelInfo bwd_info(int32_t dtype, int L) {
   return dtype == SPH_F64 ? sph::bwd_info_f64(L) : sph::bwd_info_f32(L);
 }
+sph::KernelInfo vjp_info(int32_t dtype, int L, int norm) {
+  return dtype == SPH_F64 ? sph::vjp_info_f64(L, norm) : sph::vjp_info_f32(L, norm);
+}
 sph::KernelInfo dbwd_info(int32_t dtype, int L, int norm) {
   return dtype == SPH_F64 ? sph::dbwd_info_f64(L, norm) : sph::dbwd_info_f32(L, norm);
 }
@@ -389,6 +392,32 @@ int32_t sph_backward(const void* dY, const void* grad_Y, int64_t n, int32_t l_ma
   if (grid > 0x7fffffff) return fail(SPH_ERR_INVALID, "n too large for one launch");
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, ki.lds_bytes, &p, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "backward launch");
+  return ok();
+}
+
+int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int32_t l_max, int32_t normalize,
+                            int32_t dtype, void* grad_xyz, void* stream) {
+  int32_t st = check_common(n, l_max, dtype);
+  if (st != SPH_OK) return st;
+  if ((st = check_norm(normalize)) != SPH_OK) return st;
+  if (n == 0) return ok();
+  if (xyz == nullptr || grad_Y == nullptr || grad_xyz == nullptr)
+    return fail(SPH_ERR_NULL, "xyz, grad_Y and grad_xyz are required");
+  const size_t w = elem_size(dtype);
+  const size_t K = static_cast<size_t>(sph_num_components(l_max));
+  const size_t un = static_cast<size_t>(n);
+  if (grad_xyz == xyz || grad_xyz == grad_Y) return fail(SPH_ERR_INVALID, "grad_xyz overlaps an input");
+  if ((st = check_no_overlap({{grad_xyz, un * 3 * w, "grad_xyz"}},
+                             {{xyz, un * 3 * w, "xyz"}, {grad_Y, un * K * w, "grad_Y"}})) != SPH_OK)
+    return st;
+  const sph::KernelInfo ki = vjp_info(dtype, l_max, normalize);
+  if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
+  hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
+  if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
+  sph::FwdParams p{xyz, n, l_max, nullptr, nullptr, grad_Y, grad_xyz, nullptr, 0, nullptr, ki.tile_points};
+  e = launch(ki.fn, static_cast<unsigned>(plain_grid(ceil_div(n, ki.tile_points))), ki.block, ki.lds_bytes, &p,
+             static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return device_fail(e, "vector-Jacobian launch");
   return ok();
 }
 

@@ -187,6 +187,9 @@ KernelInfo fwd_derivs_f64_n1_m2(int L, int variant);
 // asked for, tile_points points per block (the launch sets FwdParams::tile).
 KernelInfo ord_info_f32(int L, int normalize, bool store_y, bool store_dy, bool bwd);
 KernelInfo ord_info_f64(int L, int normalize, bool store_y, bool store_dy, bool bwd);
+// Backward from the points: the compile-time kernel of L, or k_ord past them.
+KernelInfo vjp_info_f32(int L, int normalize);
+KernelInfo vjp_info_f64(int L, int normalize);
 KernelInfo bwd_info_f32(int L);
 KernelInfo bwd_info_f64(int L);
 KernelInfo dbwd_info_f32(int L, int normalize);
