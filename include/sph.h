@@ -211,6 +211,26 @@ int32_t sph_e3nn_convert(int64_t n, int32_t l_max, int32_t normalization,
                          int32_t dtype, void* Y, void* dY, void* stream);
 
 /*
+ * sph_e3nn_compute -- Y[n,K] in e3nn's convention at sph_e3nn_coordinates'
+ * points, the factors of sph_e3nn_convert applied as the values are formed.
+ * sph_e3nn_vector_jacobian -- its backward from the same points:
+ * grad_xyz[i,a] = sum_k grad_Y[i,k] * dY_k/dx_a along the caller's axes, as
+ * sph_vector_jacobian without stored derivatives.
+ *   xyz_p          in  [n,3] written by sph_e3nn_coordinates
+ *   normalization  as in sph_e3nn_convert
+ *   grad_Y         in  [n,K]
+ *   Y              out [n,K]
+ *   grad_xyz       out [n,3]
+ * Errors: those of sph_compute and sph_vector_jacobian; SPH_ERR_INVALID for a
+ * bad normalization.
+ */
+int32_t sph_e3nn_compute(const void* xyz_p, int64_t n, int32_t l_max, int32_t normalize,
+                         int32_t normalization, int32_t dtype, void* Y, void* stream);
+int32_t sph_e3nn_vector_jacobian(const void* xyz_p, const void* grad_Y, int64_t n, int32_t l_max,
+                                 int32_t normalize, int32_t normalization, int32_t dtype,
+                                 void* grad_xyz, void* stream);
+
+/*
  * sph_batched_compute -- many neighbour lists in one persistent launch.
  * The points of n_env environments are concatenated (CSR): environment e
  * owns rows offsets[e] .. offsets[e+1]-1 of xyz (Sec. III: the harmonics of

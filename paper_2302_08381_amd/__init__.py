@@ -28,8 +28,10 @@ from ._native import (  # noqa: F401
     sph_compute_with_gradients,
     sph_compute_with_hessians,
     sph_double_backward,
+    sph_e3nn_compute,
     sph_e3nn_convert,
     sph_e3nn_coordinates,
+    sph_e3nn_vector_jacobian,
     sph_radial_expansion,
     sph_radial_expansion_backward,
     sph_vector_jacobian,

@@ -52,6 +52,8 @@ _SIGNATURES = {
                                               _vp, _vp]),
     "sph_e3nn_coordinates": (_i32, [_vp, _i64, _i32, _vp, _vp]),
     "sph_e3nn_convert": (_i32, [_i64, _i32, _i32, _i32, _vp, _vp, _vp]),
+    "sph_e3nn_compute": (_i32, [_vp, _i64, _i32, _i32, _i32, _i32, _vp, _vp]),
+    "sph_e3nn_vector_jacobian": (_i32, [_vp, _vp, _i64, _i32, _i32, _i32, _i32, _vp, _vp]),
     "sph_batched_set_options": (_i32, [_i32, _i32]),
     "sph_batched_get_config": (_i32, [_i32, _i32, _i32, _i32, _i32, ctypes.c_char_p, _i32]),
     "sph_batched_set_config": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _i32]),
@@ -235,6 +237,38 @@ def sph_e3nn_convert(Y: torch.Tensor, dY: torch.Tensor | None, l_max: int, norma
         _check(lib().sph_e3nn_convert(n, int(l_max), E3NN_NORMALIZATIONS[normalization], _dtype_code(Y), _ptr(Y),
                                       _ptr(dY), _stream(Y.device)))
     return Y, dY
+
+
+def sph_e3nn_compute(xyz_p: torch.Tensor, l_max: int, normalize: bool = True, normalization: str = "integral"):
+    """Y[n,K] in e3nn's convention at sph_e3nn_coordinates' points (include/sph.h: sph_e3nn_compute)."""
+    if normalization not in E3NN_NORMALIZATIONS:
+        raise ValueError(f"normalization must be one of {sorted(E3NN_NORMALIZATIONS)}")
+    _check_xyz(xyz_p)
+    n = xyz_p.shape[0]
+    K = (int(l_max) + 1) ** 2 if l_max >= 0 else 0
+    Y = torch.empty((n, K), dtype=xyz_p.dtype, device=xyz_p.device)
+    with torch.cuda.device(xyz_p.device):
+        _check(lib().sph_e3nn_compute(_ptr(xyz_p), n, int(l_max), int(bool(normalize)),
+                                      E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p), _ptr(Y),
+                                      _stream(xyz_p.device)))
+    return Y
+
+
+def sph_e3nn_vector_jacobian(xyz_p: torch.Tensor, grad_Y: torch.Tensor, l_max: int, normalize: bool = True,
+                             normalization: str = "integral"):
+    """grad_xyz[n,3] of sph_e3nn_compute, along the axes of the points before
+    sph_e3nn_coordinates (include/sph.h: sph_e3nn_vector_jacobian)."""
+    if normalization not in E3NN_NORMALIZATIONS:
+        raise ValueError(f"normalization must be one of {sorted(E3NN_NORMALIZATIONS)}")
+    _check_xyz(xyz_p)
+    n = xyz_p.shape[0]
+    _need(grad_Y, "grad_Y", (n, (int(l_max) + 1) ** 2), xyz_p.dtype, xyz_p.device)
+    grad_xyz = torch.empty((n, 3), dtype=xyz_p.dtype, device=xyz_p.device)
+    with torch.cuda.device(xyz_p.device):
+        _check(lib().sph_e3nn_vector_jacobian(_ptr(xyz_p), _ptr(grad_Y), n, int(l_max), int(bool(normalize)),
+                                              E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p),
+                                              _ptr(grad_xyz), _stream(xyz_p.device)))
+    return grad_xyz
 
 
 def sph_compute_with_hessians(xyz: torch.Tensor, l_max: int, normalize: bool = True,

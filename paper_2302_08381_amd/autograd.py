@@ -66,26 +66,25 @@ def spherical_harmonics_with_gradients(xyz: torch.Tensor, l_max: int, normalize:
 class _SphE3nn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, xyz, l_max, normalize, normalization):
-        ctx.l_max = l_max
-        xp = _native.sph_e3nn_coordinates(xyz)
-        Y, dY = _native.sph_compute_with_gradients(xp, l_max, normalize)
-        _native.sph_e3nn_convert(Y, dY, l_max, normalization)
-        ctx.save_for_backward(dY)
-        return Y
+        ctx.args = l_max, normalize, normalization
+        xp = _native.sph_e3nn_coordinates(xyz)  # a copy: the backward does not depend on the caller's tensor
+        ctx.save_for_backward(xp)
+        return _native.sph_e3nn_compute(xp, l_max, normalize, normalization)
 
     @staticmethod
     def backward(ctx, grad_Y):
-        (dY,) = ctx.saved_tensors
-        return _native.sph_backward(dY, grad_Y.contiguous(), ctx.l_max), None, None, None
+        (xp,) = ctx.saved_tensors
+        return _native.sph_e3nn_vector_jacobian(xp, grad_Y.contiguous(), *ctx.args), None, None, None
 
 
 def e3nn_spherical_harmonics(xyz: torch.Tensor, l_max: int, normalize: bool = True,
                              normalization: str = "integral") -> torch.Tensor:
     """Y[n,(l_max+1)^2] in e3nn's convention (Sec. III.B): degrees 0..l_max,
     y as the polar axis, ``normalization`` "integral", "component" or
-    "norm"; differentiable once w.r.t. xyz.  Permutation, forward and
-    conversion all run in the library's kernels (include/sph.h:
-    sph_e3nn_coordinates, sph_e3nn_convert)."""
+    "norm"; differentiable once w.r.t. xyz.  The points are permuted once; the
+    forward and the backward apply the factors as they form the values and
+    derivatives (include/sph.h: sph_e3nn_coordinates, sph_e3nn_compute,
+    sph_e3nn_vector_jacobian)."""
     if normalization not in _native.E3NN_NORMALIZATIONS:
         raise ValueError(f"normalization must be one of {sorted(_native.E3NN_NORMALIZATIONS)}")
     return _SphE3nn.apply(xyz.contiguous(), int(l_max), bool(normalize), normalization)

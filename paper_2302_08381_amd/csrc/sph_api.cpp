@@ -99,8 +99,8 @@ sph::KernelInfo fwd_info(int32_t dtype, int L, int norm, bool store_dy, bool fus
 sph::KernelInfo bwd_info(int32_t dtype, int L) {
   return dtype == SPH_F64 ? sph::bwd_info_f64(L) : sph::bwd_info_f32(L);
 }
-sph::KernelInfo vjp_info(int32_t dtype, int L, int norm) {
-  return dtype == SPH_F64 ? sph::vjp_info_f64(L, norm) : sph::vjp_info_f32(L, norm);
+sph::KernelInfo vjp_info(int32_t dtype, int L, int norm, int conv) {
+  return dtype == SPH_F64 ? sph::vjp_info_f64(L, norm, conv) : sph::vjp_info_f32(L, norm, conv);
 }
 sph::KernelInfo dbwd_info(int32_t dtype, int L, int norm) {
   return dtype == SPH_F64 ? sph::dbwd_info_f64(L, norm) : sph::dbwd_info_f32(L, norm);
@@ -337,8 +337,11 @@ const char* sph_last_error(void) { return g_last_error.c_str(); }
 
 const char* sph_version(void) { return "1.0.0 gfx950"; }
 
-int32_t sph_compute_with_gradients(const void* xyz, int64_t n, int32_t l_max, int32_t normalize,
-                                   int32_t dtype, void* Y, void* dY, void* stream) {
+namespace {
+
+// conv: FwdParams::conv (values only: dY null)
+int32_t forward(const void* xyz, int64_t n, int32_t l_max, int32_t normalize, int32_t conv, int32_t dtype, void* Y,
+                void* dY, void* stream) {
   int32_t st = check_common(n, l_max, dtype);
   if (st != SPH_OK) return st;
   if ((st = check_norm(normalize)) != SPH_OK) return st;
@@ -355,7 +358,7 @@ int32_t sph_compute_with_gradients(const void* xyz, int64_t n, int32_t l_max, in
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
-  sph::FwdParams p{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr, ki.tile_points};
+  sph::FwdParams p{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr, ki.tile_points, conv};
   const int64_t grid = plain_grid(ceil_div(n, ki.tile_points));
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, ki.lds_bytes, &p,
              static_cast<hipStream_t>(stream));
@@ -363,9 +366,16 @@ int32_t sph_compute_with_gradients(const void* xyz, int64_t n, int32_t l_max, in
   return ok();
 }
 
+}  // namespace
+
+int32_t sph_compute_with_gradients(const void* xyz, int64_t n, int32_t l_max, int32_t normalize,
+                                   int32_t dtype, void* Y, void* dY, void* stream) {
+  return forward(xyz, n, l_max, normalize, 0, dtype, Y, dY, stream);
+}
+
 int32_t sph_compute(const void* xyz, int64_t n, int32_t l_max, int32_t normalize, int32_t dtype, void* Y,
                     void* stream) {
-  return sph_compute_with_gradients(xyz, n, l_max, normalize, dtype, Y, nullptr, stream);
+  return forward(xyz, n, l_max, normalize, 0, dtype, Y, nullptr, stream);
 }
 
 int32_t sph_backward(const void* dY, const void* grad_Y, int64_t n, int32_t l_max, int32_t dtype,
@@ -395,8 +405,11 @@ int32_t sph_backward(const void* dY, const void* grad_Y, int64_t n, int32_t l_ma
   return ok();
 }
 
-int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int32_t l_max, int32_t normalize,
-                            int32_t dtype, void* grad_xyz, void* stream) {
+namespace {
+
+// conv: FwdParams::conv
+int32_t vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int32_t l_max, int32_t normalize,
+                        int32_t conv, int32_t dtype, void* grad_xyz, void* stream) {
   int32_t st = check_common(n, l_max, dtype);
   if (st != SPH_OK) return st;
   if ((st = check_norm(normalize)) != SPH_OK) return st;
@@ -410,15 +423,22 @@ int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int3
   if ((st = check_no_overlap({{grad_xyz, un * 3 * w, "grad_xyz"}},
                              {{xyz, un * 3 * w, "xyz"}, {grad_Y, un * K * w, "grad_Y"}})) != SPH_OK)
     return st;
-  const sph::KernelInfo ki = vjp_info(dtype, l_max, normalize);
+  const sph::KernelInfo ki = vjp_info(dtype, l_max, normalize, conv);
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
-  sph::FwdParams p{xyz, n, l_max, nullptr, nullptr, grad_Y, grad_xyz, nullptr, 0, nullptr, ki.tile_points};
+  sph::FwdParams p{xyz, n, l_max, nullptr, nullptr, grad_Y, grad_xyz, nullptr, 0, nullptr, ki.tile_points, conv};
   e = launch(ki.fn, static_cast<unsigned>(plain_grid(ceil_div(n, ki.tile_points))), ki.block, ki.lds_bytes, &p,
              static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "vector-Jacobian launch");
   return ok();
+}
+
+}  // namespace
+
+int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int32_t l_max, int32_t normalize,
+                            int32_t dtype, void* grad_xyz, void* stream) {
+  return vector_jacobian(xyz, grad_Y, n, l_max, normalize, 0, dtype, grad_xyz, stream);
 }
 
 int32_t sph_double_backward(const void* xyz, const void* grad_Y, const void* v, int64_t n, int32_t l_max,
@@ -516,6 +536,20 @@ int32_t sph_e3nn_convert(int64_t n, int32_t l_max, int32_t normalization, int32_
       sph::e3nn_convert_launch(dtype == SPH_F64, n, l_max, normalization, Y, dY, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "e3nn convert launch");
   return ok();
+}
+
+int32_t sph_e3nn_compute(const void* xyz_p, int64_t n, int32_t l_max, int32_t normalize, int32_t normalization,
+                         int32_t dtype, void* Y, void* stream) {
+  if (normalization < 0 || normalization > 2)
+    return fail(SPH_ERR_INVALID, "normalization must be 0 (integral), 1 (component) or 2 (norm)");
+  return forward(xyz_p, n, l_max, normalize, 1 + normalization, dtype, Y, nullptr, stream);
+}
+
+int32_t sph_e3nn_vector_jacobian(const void* xyz_p, const void* grad_Y, int64_t n, int32_t l_max, int32_t normalize,
+                                 int32_t normalization, int32_t dtype, void* grad_xyz, void* stream) {
+  if (normalization < 0 || normalization > 2)
+    return fail(SPH_ERR_INVALID, "normalization must be 0 (integral), 1 (component) or 2 (norm)");
+  return vector_jacobian(xyz_p, grad_Y, n, l_max, normalize, 1 + normalization, dtype, grad_xyz, stream);
 }
 
 int32_t sph_radial_expansion(const void* xyz, const int64_t* offsets, int64_t n_env, int64_t n_points,

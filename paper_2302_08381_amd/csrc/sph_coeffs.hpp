@@ -120,4 +120,11 @@ constexpr CoefTable<T> make_coef_table() {
   return t;
 }
 
+// e3nn's factor of degree l: 1 for "integral" (conv 1) and for this library's
+// own harmonics (conv 0), sqrt(4 pi) for "component" (2), sqrt(4 pi / (2l+1))
+// for "norm" (3).
+constexpr double conv_factor(int conv, int l) {
+  return conv == 2 ? csqrt(4.0 * kPi) : (conv == 3 ? csqrt(4.0 * kPi / double(2 * l + 1)) : 1.0);
+}
+
 }  // namespace sph

@@ -167,14 +167,15 @@ __host__ __device__ constexpr int bucket_index(int L) {
 // Entries m > l are left untouched: no caller reads them (every read of a
 // neighbouring row is guarded by the degree conditions of its formula).
 // l < 0 writes nothing.
+// scale multiplies the row (through its start: the recursion is linear).
 template <typename T, int MM>
-__device__ __forceinline__ void q_row(int l, T z, T rxy2, T (&q)[MM + 3]) {
+__device__ __forceinline__ void q_row(int l, T z, T rxy2, T (&q)[MM + 3], T scale = T(1)) {
   const CoefTable<T>& C = coef<T>();
 #pragma unroll
   for (int m = MM; m >= 0; --m) {
     if (m > l) continue;
     if (m == l) {
-      q[m] = C.qll[l];
+      q[m] = C.qll[l] * scale;
     } else if (m == l - 1) {
       q[m] = (C.b1[l][m] * z) * q[m + 1];
     } else {
@@ -210,6 +211,23 @@ __device__ __forceinline__ void q_row_any(int l, T z, T rxy2, T (&q)[MM + 3]) {
     q_row<T, MM>(l, z, rxy2, q);
   else
     q_row_rt<T, MM>(l, z, rxy2, q);
+}
+
+// conv_factor(conv, l) for an unrolled degree and a run-time (uniform) conv.
+struct ConvTable {
+  double norm[kMaxL + 1];
+};
+constexpr ConvTable make_conv_table() {
+  ConvTable t{};
+  for (int l = 0; l <= kMaxL; ++l) t.norm[l] = conv_factor(3, l);
+  return t;
+}
+constexpr ConvTable kConv = make_conv_table();
+constexpr double kConvComponent = conv_factor(2, 0);
+
+template <typename T>
+__device__ __forceinline__ T conv_scale(int conv, int l) {
+  return conv == 2 ? static_cast<T>(kConvComponent) : (conv == 3 ? static_cast<T>(kConv.norm[l]) : T(1));
 }
 
 // dst[m] = src[m] for m <= l.

@@ -50,7 +50,7 @@ __device__ __forceinline__ void values_group_ct(const Point<T>& pt, int K, int64
   T cur[MM + 3], unused[MM + 3];
 #pragma unroll
   for (int l = LA; l < LB; ++l) {
-    q_row<T, MM>(l, pt.ez, pt.rxy2, cur);
+    q_row<T, MM>(l, pt.ez, pt.rxy2, cur, conv_scale<T>(P.conv, l));
     emit_row<T, MM, 0, NORM>(l, unused, cur, pt.ex, pt.ey, pt.ez, pt.inv_r, [&](int k, T v) { row[k] = v; });
   }
   __syncthreads();

@@ -25,6 +25,8 @@ struct FwdParams {
   int64_t n_env;
   int32_t* status;        // device status word or null
   int32_t tile = 0;       // points per tile (k_ord)
+  int32_t conv = 0;       // 0: this library's harmonics; 1 + normalization: e3nn's factors, and grad_xyz along
+                          // the axes of the points before their permutation (k_fwd, k_vjp, k_ord)
 };
 
 // Largest l_max of the compile-time forward kernels; k_ord serves the rest.
@@ -188,8 +190,8 @@ KernelInfo fwd_derivs_f64_n1_m2(int L, int variant);
 KernelInfo ord_info_f32(int L, int normalize, bool store_y, bool store_dy, bool bwd);
 KernelInfo ord_info_f64(int L, int normalize, bool store_y, bool store_dy, bool bwd);
 // Backward from the points: the compile-time kernel of L, or k_ord past them.
-KernelInfo vjp_info_f32(int L, int normalize);
-KernelInfo vjp_info_f64(int L, int normalize);
+KernelInfo vjp_info_f32(int L, int normalize, int conv);
+KernelInfo vjp_info_f64(int L, int normalize, int conv);
 KernelInfo bwd_info_f32(int L);
 KernelInfo bwd_info_f64(int L);
 KernelInfo dbwd_info_f32(int L, int normalize);

@@ -88,7 +88,7 @@ struct OrdTable {
 };
 
 template <typename T>
-constexpr OrdTable<T> make_ord_table() {
+constexpr OrdTable<T> make_ord_table(int conv) {
   OrdTable<T> t{};
   for (int m = 0; m <= kMaxL; ++m) {
     // N_m^m = Qt_m^m, N_l / N_{l-1} = sqrt((2l+1)/(2l-1) (l+m)/(l-m))
@@ -96,22 +96,30 @@ constexpr OrdTable<T> make_ord_table() {
     for (int j = 1; j <= m; ++j) n *= csqrt(double(2 * j + 1) / double(2 * j));
     for (int l = m; l <= kMaxL; ++l) {
       if (l > m) n *= csqrt(double(2 * l + 1) / double(2 * l - 1) * (double(l + m) / double(l - m)));
-      t.a[l][2 * m] = static_cast<T>(n);
+      t.a[l][2 * m] = static_cast<T>(n * conv_factor(conv, l));
       t.a[l][2 * m + 1] = l + m > 0 ? static_cast<T>(1.0 / double(l + m)) : T(0);
     }
   }
   return t;
 }
 
-constexpr OrdTable<float> kOrdF = make_ord_table<float>();
-constexpr OrdTable<double> kOrdD = make_ord_table<double>();
+// One table per set of factors: this library's (and e3nn's "integral"),
+// "component", "norm".
+template <typename T>
+struct OrdTables {
+  OrdTable<T> t[3];
+};
+constexpr OrdTables<float> kOrdF = {{make_ord_table<float>(0), make_ord_table<float>(2), make_ord_table<float>(3)}};
+constexpr OrdTables<double> kOrdD = {{make_ord_table<double>(0), make_ord_table<double>(2), make_ord_table<double>(3)}};
 
 template <typename T>
-__device__ __forceinline__ constexpr const OrdTable<T>& ord_table();
-template <>
-__device__ __forceinline__ constexpr const OrdTable<float>& ord_table<float>() { return kOrdF; }
-template <>
-__device__ __forceinline__ constexpr const OrdTable<double>& ord_table<double>() { return kOrdD; }
+__device__ __forceinline__ const OrdTable<T>& ord_table(int conv) {
+  const int i = conv < 2 ? 0 : conv - 1;
+  if constexpr (sizeof(T) == 4)
+    return kOrdF.t[i];
+  else
+    return kOrdD.t[i];
+}
 
 // The arithmetic below names its fused operations instead of leaving them to
 // the compiler, whose choice depends on which outputs a kernel has: every
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord(FwdParams P) {
 
   if (P.status != nullptr && blockIdx.x == 0 && tid < kWave) check_offsets(P, tid);
 
-  const OrdTable<T>& C = ord_table<T>();
+  const OrdTable<T>& C = ord_table<T>(P.conv);
   const int half = SPLIT ? nt / 2 : nt;  // whole waves
   const int part = SPLIT ? __builtin_amdgcn_readfirstlane(tid / half) : 0;
   const int it = tid - part * half;  // (order, point) of this thread
@@ -429,7 +437,8 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord(FwdParams P) {
         const T* sp = sacc + a * (L + 1) * PT + pp;
         T v = T(0);
         for (int j = 0; j <= L; ++j) v += sp[j * PT];
-        static_cast<T*>(P.gxyz)[p0 * 3 + tid] = v;
+        // e3nn: the points are (z, x, y), so the second axis' sum is d/dx
+        static_cast<T*>(P.gxyz)[(p0 + pp) * 3 + (P.conv == 0 ? a : (a + 2) % 3)] = v;
       }
     }
     if constexpr (SY) ord_copy_out(sy, hy, gy, np * K, tid, nt);

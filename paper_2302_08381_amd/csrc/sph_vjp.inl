@@ -62,8 +62,8 @@ constexpr int vjp_stride(int K) { return K | 1; }
 //     d/dy = y D {c_m, s_m} + m Qt_l^m {-s_{m-1}, c_{m-1}}
 //     d/dz = (Cm - l z Qt_l^m) {c_m, s_m}
 // (normalised: the caller multiplies the sums by 1/r).
-template <typename T, bool NORM, int LA, int LB>
-__device__ __forceinline__ void vjp_degrees(const Point<T>& pt, const T* st, int o, T (&g)[3]) {
+template <typename T, bool NORM, bool E3, int LA, int LB>
+__device__ __forceinline__ void vjp_degrees(const Point<T>& pt, const T* st, int o, int conv, T (&g)[3]) {
   constexpr int MM = LB - 1;
   const CoefTable<T>& C = coef<T>();
   constexpr T kIS2 = T(kInvSqrt2d);
@@ -82,6 +82,7 @@ __device__ __forceinline__ void vjp_degrees(const Point<T>& pt, const T* st, int
   }
   T prev[MM + 3], cur[MM + 3];
   if constexpr (LA >= 1) q_row<T, MM>(LA - 1, ez, pt.rxy2, prev);
+  T xs = T(0), ys = T(0), zs = T(0);  // E3: the degrees done, scaled
   T x0 = T(0), y0 = T(0), z0 = T(0), x1 = T(0), y1 = T(0), z1 = T(0);
 #pragma unroll
   for (int l = LA; l < LB; ++l) {
@@ -117,29 +118,41 @@ __device__ __forceinline__ void vjp_degrees(const Point<T>& pt, const T* st, int
       }
     }
     copy_row<T, MM>(l, cur, prev);
+    if constexpr (E3) {
+      const T cl = conv_scale<T>(conv, l);
+      xs += cl * (x0 + x1);
+      ys += cl * (y0 + y1);
+      zs += cl * (z0 + z1);
+      x0 = y0 = z0 = x1 = y1 = z1 = T(0);
+    }
     // The next degree starts after this one: without this fence the unrolled
     // degrees interleave, hold most of the row in registers and spill (float
     // l_max 12, 500 000 points: 201 us against 68).
-    asm volatile("" : "+v"(ez), "+v"(o), "+v"(x0), "+v"(y0), "+v"(z0), "+v"(x1), "+v"(y1), "+v"(z1));
+    if constexpr (E3)
+      asm volatile("" : "+v"(ez), "+v"(o), "+v"(xs), "+v"(ys), "+v"(zs));
+    else
+      asm volatile("" : "+v"(ez), "+v"(o), "+v"(x0), "+v"(y0), "+v"(z0), "+v"(x1), "+v"(y1), "+v"(z1));
   }
-  g[0] += x0 + x1;
-  g[1] += y0 + y1;
-  g[2] += z0 + z1;
+  g[0] += E3 ? xs : x0 + x1;
+  g[1] += E3 ? ys : y0 + y1;
+  g[2] += E3 ? zs : z0 + z1;
 }
 
 // Wave h of the block: its part of the degrees (the branch is uniform per
 // wave).
-template <typename T, int LT, bool NORM, int DS, int... Hs>
+template <typename T, int LT, bool NORM, bool E3, int DS, int... Hs>
 __device__ __forceinline__ void vjp_parts(std::integer_sequence<int, Hs...>, int h, const Point<T>& pt,
-                                          const T* st, int o, T (&g)[3]) {
-  ((h == Hs ? vjp_degrees<T, NORM, vjp_split(LT, DS, Hs), vjp_split(LT, DS, Hs + 1)>(pt, st, o, g) : void()), ...);
+                                          const T* st, int o, int conv, T (&g)[3]) {
+  ((h == Hs ? vjp_degrees<T, NORM, E3, vjp_split(LT, DS, Hs), vjp_split(LT, DS, Hs + 1)>(pt, st, o, conv, g) : void()), ...);
 }
 
-// l_max = LT at compile time.  Dynamic LDS: 64 rows of vjp_stride(K)
+// l_max = LT at compile time.  E3: e3nn's convention (P.conv > 0), the sums
+// scaled degree by degree; carried by every kernel that cost 1-10 % (float,
+// 1e6 points: l_max 8 60 us against 56, l_max 3 16.1 against 14.5).  Dynamic LDS: 64 rows of vjp_stride(K)
 // elements, then 3 * 64 sums per wave past the first.  gY may have any
 // alignment: full tiles of 16-byte aligned arrays take the vector loads,
 // others the general copy.
-template <typename T, int LT, bool NORM, int DS>
+template <typename T, int LT, bool NORM, bool E3, int DS>
 __global__ __launch_bounds__(kWave * DS) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp(FwdParams P) {
   constexpr int K = (LT + 1) * (LT + 1);
   constexpr int S = vjp_stride(K);
@@ -190,8 +203,8 @@ __global__ __launch_bounds__(kWave * DS) __attribute__((amdgpu_waves_per_eu(2)))
     }
     __syncthreads();
     T g[3] = {T(0), T(0), T(0)};
-    vjp_parts<T, LT, NORM, DS>(std::make_integer_sequence<int, DS>{}, h, pt, st,
-                               (lane < np ? lane : np - 1) * S, g);
+    vjp_parts<T, LT, NORM, E3, DS>(std::make_integer_sequence<int, DS>{}, h, pt, st,
+                               (lane < np ? lane : np - 1) * S, P.conv, g);
     if constexpr (DS > 1) {
       if (h > 0) {
 #pragma unroll
@@ -208,7 +221,11 @@ __global__ __launch_bounds__(kWave * DS) __attribute__((amdgpu_waves_per_eu(2)))
     if (h == 0 && lane < np) {
       T* o = static_cast<T*>(P.gxyz) + (p0 + lane) * 3;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) o[a] = NORM ? g[a] * pt.inv_r : g[a];
+      for (int a = 0; a < 3; ++a) {
+        // e3nn: the points are (z, x, y), so d/dx is the second axis' sum
+        const T v = E3 ? g[(a + 1) % 3] : g[a];
+        o[a] = NORM ? v * pt.inv_r : v;
+      }
     }
     if (tile + gridDim.x < (P.n + kWave - 1) / kWave) __syncthreads();  // another tile: every read of this one is done
   }

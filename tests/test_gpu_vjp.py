@@ -68,3 +68,31 @@ def test_vector_jacobian_keeps_infinite_gradients():
         torch.cuda.synchronize()
         assert torch.equal(torch.isnan(a), torch.isnan(b))
         assert torch.equal(a[torch.isinf(b)], b[torch.isinf(b)])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("normalization", ["integral", "component", "norm"])
+@pytest.mark.parametrize("l_max", [0, 2, 8, 12, 13])
+def test_e3nn_forms_match_the_conversion(l_max, normalization, dtype):
+    """Factors applied while the values and derivatives are formed, against
+    the separate conversion of this library's outputs: both round each value
+    a few times, well inside the per-degree tolerance."""
+    import paper_2302_08381_amd as sph
+    n, K = 70, (l_max + 1) ** 2
+    xyz = to_dev(_points(n, 7400 + l_max, True), dtype)
+    xyz[3] = torch.tensor([0.0, 2.0, 0.0], dtype=dtype)  # e3nn's polar axis
+    gY = to_dev(standard_normal((n, K), 7401), dtype)
+    Yr, dYr = sph.e3nn_spherical_harmonics_with_gradients(xyz, l_max, True, normalization)
+    gr = sph.sph_backward(dYr, gY, l_max)
+    x = xyz.clone().requires_grad_(True)
+    Y = sph.e3nn_spherical_harmonics(x, l_max, True, normalization)
+    with torch.no_grad():
+        x.mul_(3.0)  # the backward's points are the forward's, whatever becomes of the caller's tensor
+    (g,) = torch.autograd.grad(Y, x, gY)
+    torch.cuda.synchronize()
+    hp, gYh = host_points(xyz[:, [2, 0, 1]].contiguous()), gY.abs().cpu().double().numpy()
+    s, gs, _ = oracle.component_scales(hp, l_max, True)
+    c = np.sqrt(4 * np.pi)  # the largest factor
+    assert (np.abs((Y.detach() - Yr).cpu().double().numpy()) / (c * s)).max() <= TOL[dtype]
+    scale = c * (gYh * gs).sum(1)[:, None] + 1e-30
+    assert (np.abs((g - gr).cpu().double().numpy()) / scale).max() <= TOL[dtype]
