@@ -459,17 +459,14 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandParams P) {
 }
 
 // One point of the expansion backward: grad_R of every degree and grad_xyz.
-// The point's radial values come from one of three sources:
-//   SRC = 0: its row in an LDS tile, [degree][NPC channels] (zero padded);
-//            grad_R goes back into the same slots, degree by degree, after
-//            they are read;
-//   SRC = 1: global memory as 16-byte vectors (channels = NPC, 16-byte
+// The point's radial values come from global memory in one of three ways:
+//   SRC = 1: as 16-byte vectors (channels = NPC, 16-byte
 //            aligned), in one of two register buffers, the next degree's
 //            loads issued before this degree's arithmetic.  Plain loads: a
 //            lane reads its 16-byte pieces of a row over several degrees,
 //            and with the nontemporal hint the lines left L2 between them
 //            and were fetched again (20-30 % slower);
-//   SRC = 2: global memory element by element (loading a degree ahead, as
+//   SRC = 2: element by element (loading a degree ahead, as
 //            for SRC = 1, was 1-4 % slower: the second buffer costs
 //            occupancy);
 //   SRC = 3: as SRC = 1 where the channels need padding but still fill
@@ -478,8 +475,7 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandParams P) {
 //            vectors past NM are zeros, never loaded or stored.
 template <typename T, int MM, bool NORM, int NPC, int SRC>
 __device__ __forceinline__ void expand_bwd_point(const T* __restrict__ xyz, const T* __restrict__ R,
-                                                 const T* __restrict__ sG, T* __restrict__ sRow,
-                                                 T* __restrict__ gxyz, T* __restrict__ gR, int64_t j, int L,
+                                                 const T* __restrict__ sG, T* __restrict__ gxyz, T* __restrict__ gR, int64_t j, int L,
                                                  int NM) {
   using V = typename Vec16<T>::type;
   constexpr int W = Vec16<T>::n;
@@ -548,15 +544,6 @@ __device__ __forceinline__ void expand_bwd_point(const T* __restrict__ xyz, cons
     }
     q_row_rt<T, MM>(l, ez, pt.rxy2, cur);
     T r[NPC], acc[NPC];
-    if constexpr (SRC == 0) {
-      const V* sv = reinterpret_cast<const V*>(sRow + l * NPC);
-#pragma unroll
-      for (int h = 0; h < NV; ++h) {
-        const V v = sv[h];
-#pragma unroll
-        for (int u = 0; u < W; ++u) r[h * W + u] = v[u];
-      }
-    }
 #pragma unroll
     for (int n = 0; n < NPC; ++n) {
       if constexpr (SRC == 1 || SRC == 3) r[n] = rc[n / W][n % W];
@@ -634,16 +621,7 @@ __device__ __forceinline__ void expand_bwd_point(const T* __restrict__ xyz, cons
       g2 += sz;
     }
     if (gRj != nullptr) {
-      if constexpr (SRC == 0) {
-        V* sv = reinterpret_cast<V*>(sRow + l * NPC);
-#pragma unroll
-        for (int h = 0; h < NV; ++h) {
-          V v;
-#pragma unroll
-          for (int u = 0; u < W; ++u) v[u] = acc[h * W + u];
-          sv[h] = v;
-        }
-      } else if constexpr (SRC == 1) {
+      if constexpr (SRC == 1) {
 #pragma unroll
         for (int h = 0; h < NV; ++h) {
           V v;
@@ -683,172 +661,43 @@ __device__ __forceinline__ void expand_bwd_point(const T* __restrict__ xyz, cons
   }
 }
 
-// Copies of one group's radial tile between global rows [cnt][L+1][NM]
-// (contiguous from src) and LDS rows of stride RS, [L+1][NPC] each (NPC >= NM,
-// the padding channels zero).  MODE 2 (NM == NPC, 16-byte aligned global
-// rows): the block as contiguous 16-byte vectors, a batch of them in flight
-// per lane.  MODE 1 (NM a whole number of vectors, aligned) and 0 (else):
-// each lane keeps one slot of U channels (a vector, or one element) and
-// walks the tile's rows, a batch in flight.  GS lanes of the group take
-// part (lane gl).
-template <typename T, int NPC, int GS, int MODE>
-__device__ __forceinline__ void expand_tile_in(T* __restrict__ sR, int RS, const T* __restrict__ src, int cnt,
-                                               int L, int NM, int gl) {
-  if constexpr (MODE == 2) {
-    using V = typename Vec16<T>::type;
-    constexpr int W = Vec16<T>::n;
-    constexpr int NB = 6;
-    const int RV = (L + 1) * NPC / W;  // vectors per row
-    const int nv = cnt * RV;
-    const V* g = reinterpret_cast<const V*>(src);
-    int p = gl / RV, c = gl - (gl / RV) * RV;
-    const int qs = GS / RV, rq = GS - qs * RV;
-    for (int i0 = gl; i0 < nv; i0 += GS * NB) {
-      V v[NB];
-      int o[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        o[u] = p * RS + c * W;
-        if (i0 + u * GS < nv) v[u] = __builtin_nontemporal_load(g + i0 + u * GS);
-        p += qs;
-        c += rq;
-        if (c >= RV) {
-          c -= RV;
-          ++p;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < NB; ++u)
-        if (i0 + u * GS < nv) *reinterpret_cast<V*>(sR + o[u]) = v[u];
-    }
-  } else {
-    // lane gl keeps the slot of channels n .. n + U - 1 (n = (gl % SL) U)
-    // and walks the rows r = p (L+1) + l of the tile, GS / SL rows per step,
-    // NB loads in flight; the slots past NM get zeros
-    constexpr int U = MODE == 1 ? Vec16<T>::n : 1;
-    using E = std::conditional_t<U == 1, T, typename Vec16<T>::type>;
-    constexpr int SL = NPC / U;
-    static_assert(GS % SL == 0, "whole rows per step");
-    constexpr int RPS = GS / SL;
-    constexpr int NB = 8;
-    E zero;
-    if constexpr (U == 1) {
-      zero = T(0);
-    } else {
-#pragma unroll
-      for (int u = 0; u < U; ++u) zero[u] = T(0);
-    }
-    const int n = (gl % SL) * U, L1 = L + 1, rows = cnt * L1;
-    int p = (gl / SL) / L1, l = gl / SL - p * L1;
-    const int qs = RPS / L1, rq = RPS - qs * L1;
-    for (int r0 = gl / SL; r0 < rows; r0 += RPS * NB) {
-      E v[NB];
-      int o[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int r = r0 + u * RPS;
-        o[u] = p * RS + l * NPC + n;
-        v[u] = r < rows && n < NM ? *reinterpret_cast<const E*>(src + r * NM + n) : zero;
-        p += qs;
-        l += rq;
-        if (l >= L1) {
-          l -= L1;
-          ++p;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < NB; ++u)
-        if (r0 + u * RPS < rows) *reinterpret_cast<E*>(sR + o[u]) = v[u];
-    }
-  }
-}
-
-template <typename T, int NPC, int GS, int MODE>
-__device__ __forceinline__ void expand_tile_out(const T* __restrict__ sR, int RS, T* __restrict__ dst, int cnt,
-                                                int L, int NM, int gl) {
-  if constexpr (MODE == 2) {
-    using V = typename Vec16<T>::type;
-    constexpr int W = Vec16<T>::n;
-    const int RV = (L + 1) * NPC / W;
-    const int nv = cnt * RV;
-    V* g = reinterpret_cast<V*>(dst);
-    int p = gl / RV, c = gl - (gl / RV) * RV;
-    const int qs = GS / RV, rq = GS - qs * RV;
-    for (int i = gl; i < nv; i += GS) {
-      g[i] = *reinterpret_cast<const V*>(sR + p * RS + c * W);
-      p += qs;
-      c += rq;
-      if (c >= RV) {
-        c -= RV;
-        ++p;
-      }
-    }
-  } else {
-    // the walk of expand_tile_in: a slot of U channels per lane, GS / SL
-    // rows a step
-    constexpr int U = MODE == 1 ? Vec16<T>::n : 1;
-    using E = std::conditional_t<U == 1, T, typename Vec16<T>::type>;
-    constexpr int SL = NPC / U;
-    constexpr int RPS = GS / SL;
-    const int n = (gl % SL) * U, L1 = L + 1, rows = cnt * L1;
-    int p = (gl / SL) / L1, l = gl / SL - p * L1;
-    const int qs = RPS / L1, rq = RPS - qs * L1;
-    if (n < NM) {
-      for (int r = gl / SL; r < rows; r += RPS) {
-        *reinterpret_cast<E*>(dst + r * NM + n) = *reinterpret_cast<const E*>(sR + p * RS + l * NPC + n);
-        p += qs;
-        l += rq;
-        if (l >= L1) {
-          l -= L1;
-          ++p;
-        }
-      }
-    }
-  }
-}
-
 // Backward of the expansion for an upstream gradient G = dL/dc (chain rule):
 //   grad_R[j, l, n] = sum_m G[e, n, l^2+l+m] Y_l^m(x_j)
 //   grad_xyz[j, a]  = sum_k gY[j, k] dY_k/dx_a(x_j),
 //                     gY[j, k] = sum_n G[e, n, k] R[j, l(k), n]
-// One lane per point; neither Y nor dY is stored.  A block is one wave split
-// into 64 / GS groups of GS lanes, each walking its own run of environments
-// (an even share of the points) in chunks of GS consecutive points.  A chunk
-// may span the end of one environment and the start of the next: the group
-// keeps the G of both in two LDS slices ([k][channel], read as 16-byte
-// vectors) and each lane reads the slice of its own point's environment.
-// Chunks that stopped at every environment's end would leave a fifth of the
-// lanes idle on environments of 8..128 points (a third with 64 lanes); where
-// two slices would not fit one block's LDS (P.slices = 1) they do stop.  Per
-// point, one pass per degree forms every value and derivative of the row at
-// once (Eq. iter-deri with the order-m factors tabulated once per point),
-// contracts it with G and the point's radial values of that degree, and
-// produces the degree's grad_R.  STAGE: each chunk's radial rows arrive in
-// an LDS tile by coalesced 16-byte copies and its grad_R leaves the same
-// way; otherwise every lane reads and writes its own rows.  NPC: channels
-// padded to a multiple of 4 (8 or 16).
-template <typename T, int MM, bool NORM, int NPC, int GS, bool STAGE>
+// The run-time-degree kernel, for the degrees past k_expbwd's (and double
+// with padded 16 channels at l_max 7 and 8, see expand_bwd_info).  One lane
+// per point; neither Y nor dY is stored.  A block is one wave that walks its
+// own run of environments (an even share of the points) in chunks of 64
+// consecutive points.  A chunk may span the end of one environment and the
+// start of the next: the block keeps the G of both in two LDS slices
+// ([k][channel], read as 16-byte vectors) and each lane reads the slice of
+// its own point's environment.  Chunks that stopped at every environment's
+// end would leave a third of the lanes idle on environments of 8..128
+// points; where two slices would not fit one block's LDS (P.slices = 1) they
+// do stop.  Per point, one pass per degree forms every value and derivative
+// of the row at once (Eq. iter-deri with the order-m factors tabulated once
+// per point), contracts it with G and the point's radial values of that
+// degree, and produces the degree's grad_R; every lane reads and writes its
+// own radial rows.  NPC: channels padded to a multiple of 4 (8 or 16).
+template <typename T, int MM, bool NORM, int NPC>
 __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NG = kWave / GS;
-  const int lane = threadIdx.x;
-  const int grp = lane / GS, gl = lane % GS;
+  constexpr int GS = kWave;
+  const int gl = threadIdx.x, lane = gl;
   const int L = P.L;
   const int K = (L + 1) * (L + 1);
   const int NM = P.n_max;
-  const int RS = expand_bwd_row_stride<T>(L, NPC);
   const size_t slice = static_cast<size_t>(K) * NPC;
   const int nsl = P.slices;  // 2: chunks may span two environments
-  T* sG = reinterpret_cast<T*>(smem) +
-          static_cast<size_t>(grp) * (nsl * slice + (STAGE ? static_cast<size_t>(GS) * RS : 0));
-  T* sR = sG + nsl * slice;
+  T* sG = reinterpret_cast<T*>(smem);
   const T* xyz = static_cast<const T*>(P.xyz);
   const T* R = static_cast<const T*>(P.R);
   const T* gc = static_cast<const T*>(P.gc);
   T* gxyz = static_cast<T*>(P.gxyz);
   T* gR = static_cast<T*>(P.gR);
   // radial rows as whole 16-byte vectors: every padded channel present and
-  // both radial arrays 16-byte aligned (uniform); vpart: the channels fill
+  // both radial arrays 16-byte aligned; vpart: the channels fill
   // whole vectors short of the padding
   const bool aligned = aligned16(R) && (gR == nullptr || aligned16(gR));
   const bool vec = NM == NPC && aligned;
@@ -862,15 +711,14 @@ __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
     if (lane == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // The groups split the points evenly: group g of G takes the environments
+  // The blocks split the points evenly: block g of G takes the environments
   // that start in points [g n / G, (g+1) n / G) (found by searching the
   // offsets; every environment has one start, so each goes to exactly one
-  // group), which keeps the two groups of a wave and all waves equally busy.
-  // Group state: environment e, its range [b, t), the chunk start j0
+  // block).  State: environment e, its range [b, t), the chunk start j0
   // (b <= j0 < t), and which environment each G slice holds.
-  const int64_t G = static_cast<int64_t>(gridDim.x) * NG, g = static_cast<int64_t>(blockIdx.x) * NG + grp;
-  int64_t e = group_lower_bound(P.offsets, P.n_env, g * P.n / G, gl, grp * GS, GS);
-  const int64_t e_last = group_lower_bound(P.offsets, P.n_env, (g + 1) * P.n / G, gl, grp * GS, GS);
+  const int64_t G = gridDim.x, g = blockIdx.x;
+  int64_t e = group_lower_bound(P.offsets, P.n_env, g * P.n / G, gl, 0, GS);
+  const int64_t e_last = group_lower_bound(P.offsets, P.n_env, (g + 1) * P.n / G, gl, 0, GS);
   const int64_t e_end = g + 1 == G ? P.n_env : e_last;
   int64_t b = 0, t = 0, j0 = 0;
   // first non-empty environment at or after ee (e_end if none), its range
@@ -924,7 +772,7 @@ __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
       }
     }
     const bool span = e2 < e_end;
-    __syncthreads();  // every read of the previous chunk's slices and tile is done
+    __syncthreads();  // every read of the previous chunk's slices is done
     if (active) {
       if (in_cur != e) {
         load_slice(se, e);
@@ -935,45 +783,18 @@ __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
         in_oth = e2;
       }
     }
-    if constexpr (STAGE) {
-      if (active) {
-        const T* src = R + j0 * (L + 1) * NM;
-        if (vec)
-          expand_tile_in<T, NPC, GS, 2>(sR, RS, src, cnt, L, NM, gl);
-        else if (vpart)
-          expand_tile_in<T, NPC, GS, 1>(sR, RS, src, cnt, L, NM, gl);
-        else
-          expand_tile_in<T, NPC, GS, 0>(sR, RS, src, cnt, L, NM, gl);
-      }
-    }
     __syncthreads();
     const int64_t j = j0 + gl;
     if (active && gl < cnt) {
       const T* sGj = sG + (j < t ? se : 1 - se) * slice;
-      if constexpr (STAGE)
-        expand_bwd_point<T, MM, NORM, NPC, 0>(xyz, R, sGj, sR + gl * RS, gxyz, gR, j, L, NM);
-      else if (vec)
-        expand_bwd_point<T, MM, NORM, NPC, 1>(xyz, R, sGj, nullptr, gxyz, gR, j, L, NM);
+      if (vec)
+        expand_bwd_point<T, MM, NORM, NPC, 1>(xyz, R, sGj, gxyz, gR, j, L, NM);
       else if (vpart)
-        expand_bwd_point<T, MM, NORM, NPC, 3>(xyz, R, sGj, nullptr, gxyz, gR, j, L, NM);
+        expand_bwd_point<T, MM, NORM, NPC, 3>(xyz, R, sGj, gxyz, gR, j, L, NM);
       else
-        expand_bwd_point<T, MM, NORM, NPC, 2>(xyz, R, sGj, nullptr, gxyz, gR, j, L, NM);
+        expand_bwd_point<T, MM, NORM, NPC, 2>(xyz, R, sGj, gxyz, gR, j, L, NM);
     }
-    if constexpr (STAGE) {
-      if (gR != nullptr) {
-        __syncthreads();  // the group's grad_R rows are in the tile
-        if (active) {
-          T* dst = gR + j0 * (L + 1) * NM;
-          if (vec)
-            expand_tile_out<T, NPC, GS, 2>(sR, RS, dst, cnt, L, NM, gl);
-          else if (vpart)
-            expand_tile_out<T, NPC, GS, 1>(sR, RS, dst, cnt, L, NM, gl);
-          else
-            expand_tile_out<T, NPC, GS, 0>(sR, RS, dst, cnt, L, NM, gl);
-        }
-      }
-    }
-    // advance the group past the chunk
+    // advance past the chunk
     if (active) {
       j0 += cnt;
       if (span) {  // the chunk ended inside e2 (or at its end): e2 becomes e

@@ -24,25 +24,32 @@ void fill_spec(const void** out, std::integer_sequence<int, Ls...>) {
   for (size_t i = 0; i < sizeof...(Ls); ++i) out[i] = tbl[i];
 }
 
-template <bool NORM, int NPC, int GS, bool STAGE, int... Is>
+// The run-time-degree backward, for the buckets that reach past the
+// compile-time one.
+template <bool NORM, int NPC, int MM>
+const void* bwd_ptr() {
+  if constexpr (MM > kCompileMax<T> || !expbwd_serves<T>(MM, NPC))
+    return reinterpret_cast<const void*>(&k_expand_bwd<T, MM, NORM, NPC>);
+  else
+    return nullptr;
+}
+
+template <bool NORM, int NPC, int... Is>
 void fill_bwd(const void** out, std::integer_sequence<int, Is...>) {
-  const void* tbl[] = {reinterpret_cast<const void*>(&k_expand_bwd<T, kBuckets[Is], NORM, NPC, GS, STAGE>)...};
+  const void* tbl[] = {bwd_ptr<NORM, NPC, kBuckets[Is]>()...};
   for (size_t i = 0; i < sizeof...(Is); ++i) out[i] = tbl[i];
 }
 
 struct Tables {
   const void* fn[2][2][kNumBuckets];  // [normalize][ACC == 8]
   const void* spec[2][2][kSpecMax + 1];
-  const void* bwd[2][2][2][kNumBuckets];  // [normalize][NPC == 16][staged two groups, or one direct group]
+  const void* bwd[2][2][kNumBuckets];  // [normalize][NPC == 16]
   Tables() {
-    fill_bwd<false, 8, 32, true>(bwd[0][0][0], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<true, 8, 32, true>(bwd[1][0][0], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<false, 16, 32, true>(bwd[0][1][0], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<true, 16, 32, true>(bwd[1][1][0], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<false, 8, 64, false>(bwd[0][0][1], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<true, 8, 64, false>(bwd[1][0][1], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<false, 16, 64, false>(bwd[0][1][1], std::make_integer_sequence<int, kNumBuckets>{});
-    fill_bwd<true, 16, 64, false>(bwd[1][1][1], std::make_integer_sequence<int, kNumBuckets>{});
+    using Is = std::make_integer_sequence<int, kNumBuckets>;
+    fill_bwd<false, 8>(bwd[0][0], Is{});
+    fill_bwd<true, 8>(bwd[1][0], Is{});
+    fill_bwd<false, 16>(bwd[0][1], Is{});
+    fill_bwd<true, 16>(bwd[1][1], Is{});
     fill_expand<false, 4>(fn[0][0], std::make_integer_sequence<int, kNumBuckets>{});
     fill_expand<true, 4>(fn[1][0], std::make_integer_sequence<int, kNumBuckets>{});
     fill_expand<false, 8>(fn[0][1], std::make_integer_sequence<int, kNumBuckets>{});
@@ -69,32 +76,24 @@ KernelInfo expand_info_f64(int L, int normalize, int n_max) {
   return KernelInfo{fn, 0, 0, 0, kExpandThreads};
 }
 
-KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max) {
+KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env) {
   if (L < 0 || L > kMaxLmax || (normalize != 0 && normalize != 1) || n_max < 1 || n_max > 16)
     return KernelInfo{nullptr, 0, 0, 0, 0};
-  const Tables& t = tables();
-  const int w = n_max > 8 ? 1 : 0;
-  const int npc = w ? 16 : 8;
-  // Two staged groups of 32 lanes per wave where their G slices and radial
-  // tiles take at most 32 KiB (five waves per CU), else one group of 64
-  // lanes reading its rows directly, whose LDS holds only G.  Measured on
-  // 20 000 environments: staged faster up to 29.8 KB (float32 l_max 8 with 8
-  // channels 506 vs 517 us; float64 l_max 4, float32 16 channels l_max 4),
-  // direct from 34 KB (float32 l_max 9 712 vs 546 us, l_max 12 1362 vs 773;
-  // float64 l_max 8 1328 vs 678).  Padded channels (n_max < npc) copy
-  // their tiles element by element, and float32 staging still paid at
-  // 39-42 KB (12 channels l_max 6 1016 vs 1116 us, 5 channels l_max 10 873
-  // vs 895) but not from 49 KB (l_max 12 1408 vs 1068); float64 lost at
-  // 42 KB (5 channels l_max 6 692 vs 678).  The limit is the largest size
-  // measured to gain, 42240 bytes.
-  const size_t limit = n_max < npc && sizeof(T) == 4 ? 42240 : 32 * 1024;
-  const int direct = expand_bwd_lds_bytes<T>(L, npc, 32, true) > limit ? 1 : 0;
-  const int gs = direct ? 64 : 32;
-  // one G slice per group where two would not fit (chunks then stop at
-  // every environment's end)
-  const int slices = expand_bwd_lds_bytes<T>(L, npc, gs, !direct, 2) <= 160 * 1024 ? 2 : 1;
-  KernelInfo ki{t.bwd[normalize][w][direct][bucket_index(L)], expand_bwd_lds_bytes<T>(L, npc, gs, !direct, slices),
-                0, 64 / gs, kWave};
+  const int npc = n_max > 8 ? 16 : 8;
+  if (expbwd_serves<T>(L, npc)) {
+    const bool vec = n_max == npc && aligned;
+    const void* fn = normalize ? expbwd_fn_f64_n1(L, npc, vec) : expbwd_fn_f64_n0(L, npc, vec);
+    const int waves = expbwd_waves<T>(L, npc);
+    const int slices = expbwd_slices<T>(npc, n, n_env);
+    KernelInfo ki{fn, expbwd_lds_bytes<T>(L, npc, slices, waves), 0, 1, kWave * waves};
+    ki.slices = slices;
+    return ki;
+  }
+  // one G slice where two would not fit (chunks then stop at every
+  // environment's end)
+  const int slices = expand_bwd_lds_bytes<T>(L, npc, 2) <= 160 * 1024 ? 2 : 1;
+  KernelInfo ki{tables().bwd[normalize][npc == 16 ? 1 : 0][bucket_index(L)], expand_bwd_lds_bytes<T>(L, npc, slices), 0, 1,
+                kWave};
   ki.slices = slices;
   return ki;
 }

@@ -111,7 +111,7 @@ struct ExpandBwdParams {
   void* gxyz;              // [n,3] or null
   void* gR;                // [n, L+1, n_max] or null
   int32_t* status;         // device status word or null
-  int32_t slices;          // G slices per lane group: 2 (chunks may span two environments) or 1
+  int32_t slices;          // G slices: environments a chunk may run through
 };
 // Row stride (elements) of the backward's LDS radial tile: (L+1) * np
 // channels, padded so that a row spans an odd number of 16-byte vectors
@@ -122,15 +122,51 @@ __host__ __device__ constexpr int expand_bwd_row_stride(int L, int np) {
   const int s = (L + 1) * np;
   return (s / W) % 2 == 1 ? s : s + W;
 }
-// LDS of one backward block (one wave in groups of gs lanes): each group's
-// environment gradients G as [K][np], `slices` of them (two where a chunk
-// may span two environments), and, when staged, its radial tile of gs rows.
+// LDS of one block of the run-time-degree backward: `slices` environment
+// gradients G as [K][np] (two where a chunk may span two environments).
 template <typename T>
-__host__ __device__ constexpr size_t expand_bwd_lds_bytes(int L, int np, int gs, bool stage, int slices = 2) {
-  const int K = (L + 1) * (L + 1);
-  const size_t per = static_cast<size_t>(slices) * K * np +
-                     (stage ? static_cast<size_t>(gs) * expand_bwd_row_stride<T>(L, np) : 0);
-  return sizeof(T) * static_cast<size_t>(64 / gs) * per;
+__host__ __device__ constexpr size_t expand_bwd_lds_bytes(int L, int np, int slices) {
+  return sizeof(T) * static_cast<size_t>(slices) * (L + 1) * (L + 1) * np;
+}
+
+// The compile-time backward (k_expbwd): environments a chunk may run through,
+// and its LDS: the radial tile of 64 points, `slices` G slices and the sums of
+// the waves past the first.
+constexpr int kExpBwdSlices = 4;
+// Waves that share a tile's degrees.  Twice the waves of a CU on the same LDS,
+// against order-m tables formed twice.  Float, 20 000 environments, 1 / 2 / 4
+// waves: 8 channels l_max 3 72 / 73 us, l_max 4 88.7 / 88.6, l_max 8 - / 210 /
+// 240, l_max 12 - / 455 / 339; 16 channels (10 000) l_max 12 - / 832 / 508.
+// Double, 8 channels l_max 3 180 / 201, l_max 8 - / 490 / 612.
+template <typename T>
+constexpr int expbwd_waves(int L, int npc) {
+  if (L <= (npc == 8 ? (sizeof(T) == 4 ? 4 : 5) : 3)) return 1;
+  return sizeof(T) == 4 && L >= (npc == 8 ? 12 : 11) ? 4 : 2;
+}
+// Environments per chunk: four with 8 channels (l_max 8 float 210 us against
+// 221 with two, double 490 and 533; all eight that a wider walk would allow
+// cost 2-3 % there), two with 16, whose slices would cost blocks (float
+// l_max 6 367 us against 415 with four), unless the environments have under 12
+// points on average and two would leave most lanes idle (16 channels, l_max 6,
+// 100 000 environments of 6 points: float 367 us with four, 479 with two;
+// double 676 with three, 886 with two).
+template <typename T>
+constexpr int expbwd_slices(int npc, int64_t n, int64_t n_env) {
+  if (npc == 8) return kExpBwdSlices;
+  return n / (n_env > 0 ? n_env : 1) >= 12 ? 2 : (sizeof(T) == 4 ? 4 : 3);
+}
+// Where the compile-time kernel is the faster one: up to kCompileMax, but not
+// double with 16 channels past l_max 6, whose registers spill (10 000
+// environments, l_max 8: 716 us against the run-time-degree kernel's 539;
+// l_max 6 356 against 400).
+template <typename T>
+constexpr bool expbwd_serves(int L, int npc) {
+  return L <= kCompileMax<T> && !(sizeof(T) == 8 && npc == 16 && L >= 7);
+}
+template <typename T>
+constexpr size_t expbwd_lds_bytes(int L, int np, int slices, int waves) {
+  return sizeof(T) * (static_cast<size_t>(64) * expand_bwd_row_stride<T>(L, np) +
+                      static_cast<size_t>(slices) * (L + 1) * (L + 1) * np + static_cast<size_t>(3 * 64) * (waves - 1));
 }
 
 // A kernel's host stub, its dynamic LDS bytes (for the l_max it was looked
@@ -144,7 +180,7 @@ struct KernelInfo {
   int tile_points;
   int block;
   int blocks_per_cu = 0;  // plain calls: 1: a resident grid (occupancy x CUs) loops over tiles; 0: one tile per block
-  int slices = 0;         // the expansion backward: G slices per lane group
+  int slices = 0;         // the expansion backward: G slices per block
 };
 
 // Per element type (suffix f32 / f64) and normalisation; fn == nullptr when
@@ -208,11 +244,16 @@ KernelInfo hess_info_f64(int L, int normalize);
 // expand_lds_bytes), block = 128 threads.
 KernelInfo expand_info_f32(int L, int normalize, int n_max);
 KernelInfo expand_info_f64(int L, int normalize, int n_max);
-// Its backward: channels padded to 8 or 16 (n_max <= 16); tile_points holds
-// the lane groups per block, slices the G slices per group (two unless two
-// do not fit one block's LDS).
-KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max);
-KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max);
+// Its backward: channels padded to 8 or 16 (n_max <= 16); aligned: R and
+// grad_R start on 16-byte boundaries; slices: the G slices of a block.
+KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);
+KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);
+// The compile-time backward (L <= kCompileMax): the padded channel count npc
+// (8 or 16), with or without the whole-vector copies.
+const void* expbwd_fn_f32_n0(int L, int npc, bool vec);
+const void* expbwd_fn_f32_n1(int L, int npc, bool vec);
+const void* expbwd_fn_f64_n0(int L, int npc, bool vec);
+const void* expbwd_fn_f64_n1(int L, int npc, bool vec);
 // e3nn's conventions: the permuted coordinates and the in-place conversion
 // of Y and dY (dtype64: double, else float).
 hipError_t e3nn_coordinates_launch(int dtype64, const void* xyz, int64_t n, void* out, hipStream_t s);
