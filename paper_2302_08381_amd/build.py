@@ -48,6 +48,10 @@ SOURCES = [
     "sph_kernels_ord_f64.hip",
     "sph_kernels_expand_f32.hip",
     "sph_kernels_expand_f64.hip",
+    "sph_kernels_expfwd_f32_n0.hip",
+    "sph_kernels_expfwd_f32_n1.hip",
+    "sph_kernels_expfwd_f64_n0.hip",
+    "sph_kernels_expfwd_f64_n1.hip",
     "sph_kernels_expbwd_f32_n0.hip",
     "sph_kernels_expbwd_f32_n1.hip",
     "sph_kernels_expbwd_f64_n0.hip",

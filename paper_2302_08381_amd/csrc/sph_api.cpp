@@ -573,18 +573,20 @@ int32_t sph_radial_expansion(const void* xyz, const int64_t* offsets, int64_t n_
                               {offsets, (ue + 1) * 8, "offsets"}, {c, ue * n_max * K * w, "c"},
                               {status, status ? size_t(4) : size_t(0), "status"}})) != SPH_OK)
     return st;
-  const sph::KernelInfo ki = dtype == SPH_F64 ? sph::expand_info_f64(l_max, normalize, n_max)
-                                              : sph::expand_info_f32(l_max, normalize, n_max);
+  const bool aligned = reinterpret_cast<uintptr_t>(R) % 16 == 0;
+  const sph::KernelInfo ki = dtype == SPH_F64 ? sph::expand_info_f64(l_max, normalize, n_max, aligned, n_env)
+                                              : sph::expand_info_f32(l_max, normalize, n_max, aligned, n_env);
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
-  // The largest chunk (points per LDS tile) within 64 KiB, two blocks per
-  // CU; else an 8-point chunk within the 160 KiB of one CU.
+  // Where the kernel has no LDS size of its own: the largest chunk (points per
+  // LDS tile) within 64 KiB, two blocks per CU; else an 8-point chunk within
+  // the 160 KiB of one CU.
   auto lds_of = [&](int chunk) {
     return dtype == SPH_F64 ? sph::expand_lds_bytes<double>(l_max, n_max, chunk)
                             : sph::expand_lds_bytes<float>(l_max, n_max, chunk);
   };
   int chunk = 128;
   while (chunk > 8 && lds_of(chunk) > 64 * 1024) chunk /= 2;
-  const size_t lds = lds_of(chunk);
+  const size_t lds = ki.lds_bytes != 0 ? ki.lds_bytes : lds_of(chunk);
   if (lds > 160 * 1024) return fail(SPH_ERR_INVALID, "l_max and n_max need more LDS than one block has");
   hipError_t e = ensure_lds(ki.fn, lds);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");

@@ -152,6 +152,20 @@ __host__ __device__ constexpr int tile_stride(int L, int budget) {
   return plan_stride(L, budget);
 }
 
+// First degree of part i of D of the degrees 0..LT: the l whose first column
+// l^2 is nearest to i K / D.
+constexpr int degree_split(int LT, int D, int i) {
+  if (i <= 0) return 0;
+  if (i >= D) return LT + 1;
+  const int K = (LT + 1) * (LT + 1);
+  int best = 1;
+  for (int l = 1; l <= LT; ++l) {
+    const int d = D * l * l - i * K, db = D * best * best - i * K;
+    if ((d < 0 ? -d : d) < (db < 0 ? -db : db)) best = l;
+  }
+  return best;
+}
+
 // m-extent buckets: a kernel instantiated for MM serves every l_max <= MM
 // (its m loops are unrolled to MM and exit at the row's degree).
 constexpr int kNumBuckets = 8;

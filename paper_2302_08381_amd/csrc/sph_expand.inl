@@ -2,7 +2,10 @@
 //   c[e, n, l^2+l+m] = sum over the points j of environment e of
 //                      R[j, l, n] * Y_l^m(x_j)
 // with the radial values R[j, l, n] supplied by the caller, and its
-// backward.  The harmonics never leave the chip.  Forward: a block takes one
+// backward, for the degrees and channels that the compile-time kernels
+// (k_expfwd, k_expbwd) leave: degrees past kCompileMax, and in the forward
+// more than 16 channels.  The harmonics never leave the chip.  Forward: a
+// block takes one
 // environment at a time, writes the values of a chunk of its points into an
 // LDS tile, copies the chunk's radial values next to it, and contracts the
 // two tiles into per-thread accumulators; partial sums of environments
@@ -21,6 +24,63 @@ constexpr int kExpandThreads = 128;  // two waves
 // l_max = 8 with 8 channels in float, a 32-point one in double)
 template <typename T>
 inline constexpr int kExpandRBatch = std::is_same_v<T, float> ? 40 : 24;
+
+// A value that every lane holds, in scalar registers: what the walk reads from
+// the offsets would otherwise sit in vector registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
+  const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
+  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// Copy of a radial tile from global rows [cnt][L+1][NM] (from src) into LDS
+// rows of stride RS, [L+1][NPC] each: the first `lim` channels of every row
+// (lim <= NM, NPC), the padding channels zero.  MODE 1 (NM and lim whole
+// numbers of vectors, src aligned) and 0 (else): each of the NT threads keeps
+// one slot of U channels (a vector, or one element) and walks the tile's
+// rows, a batch in flight.
+template <typename T, int NPC, int NT, int MODE>
+__device__ __forceinline__ void expand_tile_in(T* __restrict__ sR, int RS, const T* __restrict__ src, int cnt,
+                                               int L, int NM, int gl) {
+  // thread gl keeps the slot of channels n .. n + U - 1 (n = (gl % SL) U)
+  // and walks the rows r = p (L+1) + l of the tile, NT / SL rows per step,
+  // NB loads in flight; the slots past NM get zeros
+  constexpr int U = MODE == 1 ? Vec16<T>::n : 1;
+  using E = std::conditional_t<U == 1, T, typename Vec16<T>::type>;
+  constexpr int SL = NPC / U;
+  static_assert(NT % SL == 0, "whole rows per step");
+  constexpr int RPS = NT / SL;
+  constexpr int NB = 8;
+  E zero;
+  if constexpr (U == 1) {
+    zero = T(0);
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u) zero[u] = T(0);
+  }
+  const int n = (gl % SL) * U, L1 = L + 1, rows = cnt * L1;
+  int p = (gl / SL) / L1, l = gl / SL - p * L1;
+  const int qs = RPS / L1, rq = RPS - qs * L1;
+  for (int r0 = gl / SL; r0 < rows; r0 += RPS * NB) {
+    E v[NB];
+    int o[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int r = r0 + u * RPS;
+      o[u] = p * RS + l * NPC + n;
+      v[u] = r < rows && n < NM ? *reinterpret_cast<const E*>(src + r * NM + n) : zero;
+      p += qs;
+      l += rq;
+      if (l >= L1) {
+        l -= L1;
+        ++p;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      if (r0 + u * RPS < rows) *reinterpret_cast<E*>(sR + o[u]) = v[u];
+  }
+}
 
 // Environment e's point range, clamped into [0, n] so that inconsistent
 // offsets (reported through the status word) never index out of bounds.

@@ -29,58 +29,10 @@ namespace sph {
 
 constexpr int kExpBwdPoints = kWave;  // points per chunk
 
-// Copies of a radial tile between global rows [cnt][L+1][NM] (contiguous from
-// src) and LDS rows of stride RS, [L+1][NPC] each (NPC >= NM, the padding
-// channels zero).  MODE 1 (NM a whole number of vectors, aligned) and 0
-// (else): each of the NT threads keeps one slot of U channels (a vector, or
-// one element) and walks the tile's rows, a batch in flight.
-template <typename T, int NPC, int NT, int MODE>
-__device__ __forceinline__ void expand_tile_in(T* __restrict__ sR, int RS, const T* __restrict__ src, int cnt,
-                                               int L, int NM, int gl) {
-  // thread gl keeps the slot of channels n .. n + U - 1 (n = (gl % SL) U)
-  // and walks the rows r = p (L+1) + l of the tile, NT / SL rows per step,
-  // NB loads in flight; the slots past NM get zeros
-  constexpr int U = MODE == 1 ? Vec16<T>::n : 1;
-  using E = std::conditional_t<U == 1, T, typename Vec16<T>::type>;
-  constexpr int SL = NPC / U;
-  static_assert(NT % SL == 0, "whole rows per step");
-  constexpr int RPS = NT / SL;
-  constexpr int NB = 8;
-  E zero;
-  if constexpr (U == 1) {
-    zero = T(0);
-  } else {
-#pragma unroll
-    for (int u = 0; u < U; ++u) zero[u] = T(0);
-  }
-  const int n = (gl % SL) * U, L1 = L + 1, rows = cnt * L1;
-  int p = (gl / SL) / L1, l = gl / SL - p * L1;
-  const int qs = RPS / L1, rq = RPS - qs * L1;
-  for (int r0 = gl / SL; r0 < rows; r0 += RPS * NB) {
-    E v[NB];
-    int o[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int r = r0 + u * RPS;
-      o[u] = p * RS + l * NPC + n;
-      v[u] = r < rows && n < NM ? *reinterpret_cast<const E*>(src + r * NM + n) : zero;
-      p += qs;
-      l += rq;
-      if (l >= L1) {
-        l -= L1;
-        ++p;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-      if (r0 + u * RPS < rows) *reinterpret_cast<E*>(sR + o[u]) = v[u];
-  }
-}
-
+// The copy back, by expand_tile_in's walk.
 template <typename T, int NPC, int NT, int MODE>
 __device__ __forceinline__ void expand_tile_out(const T* __restrict__ sR, int RS, T* __restrict__ dst, int cnt,
                                                 int L, int NM, int gl) {
-  // the walk of expand_tile_in
   constexpr int U = MODE == 1 ? Vec16<T>::n : 1;
   using E = std::conditional_t<U == 1, T, typename Vec16<T>::type>;
   constexpr int SL = NPC / U;
@@ -101,30 +53,9 @@ __device__ __forceinline__ void expand_tile_out(const T* __restrict__ sR, int RS
   }
 }
 
-// A value that every lane holds, in scalar registers: what the walk reads from
-// the offsets would otherwise sit in vector registers.
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
-  const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
-  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // Radial vectors in flight per thread for the next chunk (an l_max 8 tile of
 // 8 channels takes 9 in float on two waves, 9 in double on four).
 constexpr int kExpBwdBatch = 10;
-
-// First degree of part i of D, balanced by columns (as vjp_split).
-constexpr int expbwd_split(int LT, int D, int i) {
-  if (i <= 0) return 0;
-  if (i >= D) return LT + 1;
-  const int K = (LT + 1) * (LT + 1);
-  int best = 1;
-  for (int l = 1; l <= LT; ++l) {
-    const int d = D * l * l - i * K, db = D * best * best - i * K;
-    if ((d < 0 ? -d : d) < (db < 0 ? -db : db)) best = l;
-  }
-  return best;
-}
 
 // Whether whole-vector rows take the VEC kernel: not float with 16 channels
 // past l_max 4, where its prefetched rows make the unrolled degrees spill
@@ -250,7 +181,7 @@ __device__ __forceinline__ void expbwd_degrees(const Point<T>& pt, const T* st, 
 template <typename T, int LT, bool NORM, int NPC, int DS, int... Hs>
 __device__ __forceinline__ void expbwd_parts(std::integer_sequence<int, Hs...>, int h, const Point<T>& pt, T* st,
                                              int og, int orow, T (&g)[3]) {
-  ((h == Hs ? expbwd_degrees<T, NORM, NPC, expbwd_split(LT, DS, Hs), expbwd_split(LT, DS, Hs + 1)>(pt, st, og, orow,
+  ((h == Hs ? expbwd_degrees<T, NORM, NPC, degree_split(LT, DS, Hs), degree_split(LT, DS, Hs + 1)>(pt, st, og, orow,
                                                                                                  g, st)
             : void()),
    ...);

@@ -18,9 +18,18 @@ void fill_expand(const void** out, std::integer_sequence<int, Is...>) {
   for (size_t i = 0; i < sizeof...(Is); ++i) out[i] = tbl[i];
 }
 
+// The compile-time degrees serve more than 16 channels here.
+template <bool NORM, int ACC, int LT>
+const void* spec_ptr() {
+  if constexpr (ACC == 8 || expand_acc(LT, kExpFwdChannels + 1) == 4)
+    return reinterpret_cast<const void*>(&k_expand<T, LT, LT, NORM, ACC>);
+  else
+    return nullptr;
+}
+
 template <bool NORM, int ACC, int... Ls>
 void fill_spec(const void** out, std::integer_sequence<int, Ls...>) {
-  const void* tbl[] = {reinterpret_cast<const void*>(&k_expand<T, Ls, Ls, NORM, ACC>)...};
+  const void* tbl[] = {spec_ptr<NORM, ACC, Ls>()...};
   for (size_t i = 0; i < sizeof...(Ls); ++i) out[i] = tbl[i];
 }
 
@@ -68,9 +77,11 @@ const Tables& tables() {
 
 }  // namespace
 
-KernelInfo expand_info_f64(int L, int normalize, int n_max) {
-  const Tables& t = tables();
+KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n_env) {
   if (L < 0 || L > kMaxLmax || (normalize != 0 && normalize != 1) || n_max < 1) return KernelInfo{nullptr, 0, 0, 0, 0};
+  if (expfwd_serves<T>(L, n_max))
+    return normalize ? expfwd_info_f64_n1(L, n_max, aligned, n_env) : expfwd_info_f64_n0(L, n_max, aligned, n_env);
+  const Tables& t = tables();
   const int a = expand_acc(L, n_max) == 8 ? 1 : 0;
   const void* fn = L <= kSpecMax ? t.spec[normalize][a][L] : t.fn[normalize][a][bucket_index(L)];
   return KernelInfo{fn, 0, 0, 0, kExpandThreads};

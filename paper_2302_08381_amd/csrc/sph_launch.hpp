@@ -98,6 +98,22 @@ __host__ __device__ constexpr size_t expand_lds_bytes(int L, int n_max, int chun
   return ytile + sizeof(T) * (static_cast<size_t>(chunk) * (L + 1) * np + static_cast<size_t>(np) * K);
 }
 
+// Where the compile-time kernel (k_expfwd) serves: up to kCompileMax and 16
+// channels (24 channels, float l_max 8, 5000 environments: 131 us in k_expand
+// against 145 as two groups of 16).
+constexpr int kExpFwdChannels = 16;
+template <typename T>
+constexpr bool expfwd_serves(int L, int n_max) {
+  return L <= kCompileMax<T> && n_max <= kExpFwdChannels;
+}
+// Its waves.  Up to l_max 4 two, whose blocks are more numerous (8 channels,
+// 20 000 environments of 68 points, two / four waves: float l_max 4 55 / 65
+// us, l_max 6 91 / 87, double l_max 4 112 / 161), unless the environments
+// leave CUs without a second block (float l_max 4: 10 environments of 20 000
+// points 525 / 430 us, 300 of 600 21 / 18, 700 of 600 23 / 22) or there are
+// more channels (12, float l_max 4: 83 / 80).
+constexpr int expfwd_waves(int L, int n_max, int64_t n_env) { return L <= 4 && n_max <= 8 && n_env > 512 ? 2 : 4; }
+
 // Backward of the radial expansion (k_expand_bwd).
 struct ExpandBwdParams {
   const void* xyz;         // [n,3]
@@ -237,13 +253,17 @@ KernelInfo dbwd_info_f64(int L, int normalize);
 // group of degrees; tile_points = 16.
 KernelInfo hess_info_f32(int L, int normalize);
 KernelInfo hess_info_f64(int L, int normalize);
-// Radial expansion: the compile-time kernel of L (float L <= 12, double
-// L <= 8), else the one of the m-extent bucket of L (run-time degree), with
-// the accumulator width expand_acc(L, n_max);
-// lds_bytes is left 0 (it depends on n_max and the chunk, see
-// expand_lds_bytes), block = 128 threads.
-KernelInfo expand_info_f32(int L, int normalize, int n_max);
-KernelInfo expand_info_f64(int L, int normalize, int n_max);
+// Radial expansion: k_expfwd where it serves (lds_bytes set; aligned: R starts
+// on a 16-byte boundary); else k_expand, compile-time degrees for float
+// L <= 12 and double L <= 8, the m-extent bucket of L past them, with the
+// accumulator width expand_acc(L, n_max), block = 128 threads and lds_bytes
+// left 0 (they depend on n_max and the chunk, see expand_lds_bytes).
+KernelInfo expand_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n_env);
+KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n_env);
+KernelInfo expfwd_info_f32_n0(int L, int n_max, bool aligned, int64_t n_env);
+KernelInfo expfwd_info_f32_n1(int L, int n_max, bool aligned, int64_t n_env);
+KernelInfo expfwd_info_f64_n0(int L, int n_max, bool aligned, int64_t n_env);
+KernelInfo expfwd_info_f64_n1(int L, int n_max, bool aligned, int64_t n_env);
 // Its backward: channels padded to 8 or 16 (n_max <= 16); aligned: R and
 // grad_R start on 16-byte boundaries; slices: the G slices of a block.
 KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);

@@ -26,20 +26,6 @@ namespace sph {
 
 constexpr int kVjpPoints = kWave;  // points per tile
 
-// First degree of part i of D: the l whose first column l^2 is nearest to
-// i K / D.
-constexpr int vjp_split(int LT, int D, int i) {
-  if (i <= 0) return 0;
-  if (i >= D) return LT + 1;
-  const int K = (LT + 1) * (LT + 1);
-  int best = 1;
-  for (int l = 1; l <= LT; ++l) {
-    const int d = D * l * l - i * K, db = D * best * best - i * K;
-    if ((d < 0 ? -d : d) < (db < 0 ? -db : db)) best = l;
-  }
-  return best;
-}
-
 // Waves per tile.  One for l_max <= 3 (l_max 3, float, 1e6 points: 13.4 us
 // against 14.6 with two), four for double l_max 8, where two waves spill at
 // two per SIMD (300 000 points: 41 us against 46 at one per SIMD), else two
@@ -143,7 +129,7 @@ __device__ __forceinline__ void vjp_degrees(const Point<T>& pt, const T* st, int
 template <typename T, int LT, bool NORM, bool E3, int DS, int... Hs>
 __device__ __forceinline__ void vjp_parts(std::integer_sequence<int, Hs...>, int h, const Point<T>& pt,
                                           const T* st, int o, int conv, T (&g)[3]) {
-  ((h == Hs ? vjp_degrees<T, NORM, E3, vjp_split(LT, DS, Hs), vjp_split(LT, DS, Hs + 1)>(pt, st, o, conv, g) : void()), ...);
+  ((h == Hs ? vjp_degrees<T, NORM, E3, degree_split(LT, DS, Hs), degree_split(LT, DS, Hs + 1)>(pt, st, o, conv, g) : void()), ...);
 }
 
 // l_max = LT at compile time.  E3: e3nn's convention (P.conv > 0), the sums

@@ -1,6 +1,6 @@
-"""The compile-time backward of the radial expansion at the edges of its walk:
-chunks of up to 64 points through up to four environments, windows of 64
-environments."""
+"""The compile-time radial expansion and its backward at the edges of their
+walks: chunks of up to 64 (or 32) points, in the backward through up to four
+environments, windows of 64 environments."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,7 @@ import torch
 from workloads import standard_normal
 
 from _gpu_common import host_points, to_dev
-from test_gpu_expansion import _case, _check_backward
+from test_gpu_expansion import _case, _check, _check_backward
 
 pytestmark = pytest.mark.gpu
 
@@ -20,7 +20,30 @@ COUNTS = {
     "empties": [0] * 70 + [5] + [0] * 200 + [3, 0, 0, 130] + [0] * 63 + [2] + [0] * 64 + [1] + [0] * 90,
     "one": [1],
     "long": [700],
+    # enough environments for the two-wave blocks of low degrees
+    "many": [3, 1, 0, 2, 70] * 120,
 }
+
+
+# both sides of the channel layouts (4, 8, 12, 16 channels), of the degrees at
+# which three groups of four need more than the block's threads, and of the
+# largest degrees and channels that the compile-time kernel takes
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64])
+@pytest.mark.parametrize("l_max,n_max", [(0, 1), (0, 16), (1, 4), (3, 9), (5, 8), (6, 5), (8, 12), (8, 16), (9, 3), (11, 12),
+                                         (12, 12), (12, 16), (13, 8), (4, 17)])
+@pytest.mark.parametrize("counts", sorted(COUNTS))
+def test_forward_walk(counts, l_max, n_max, dt):
+    import paper_2302_08381_amd as sph
+    print(f"expansion walk {counts} l_max={l_max} n_max={n_max} {dt}", flush=True)
+    pts, offs, R = _case(COUNTS[counts], l_max, n_max, 1800 + l_max)
+    xyz, Rt, o = to_dev(pts, dt), to_dev(R, dt), torch.as_tensor(offs, device="cuda")
+    c = torch.full((offs.size - 1, n_max, (l_max + 1) ** 2), float("nan"), dtype=dt, device="cuda")
+    sph.sph_radial_expansion(xyz, o, Rt, l_max, l_max % 2 == 0, out=c)
+    again = sph.sph_radial_expansion(xyz, o, Rt, l_max, l_max % 2 == 0)
+    torch.cuda.synchronize()
+    assert torch.equal(c, again)
+    _check(c, host_points(xyz), offs, Rt.cpu().double().numpy(), l_max, l_max % 2 == 0, dt,
+           f"{counts} {dt} L={l_max} n={n_max}")
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64])
@@ -52,5 +75,8 @@ def test_backward_inconsistent_offsets_stay_inside():
         G = to_dev(standard_normal((3, NM, (L + 1) ** 2), 1751), torch.float32)
         st = torch.full((1,), -1, dtype=torch.int32, device="cuda")
         sph.sph_radial_expansion_backward(xyz, torch.tensor(bad, device="cuda"), Rt, G, L, True, status=st)
+        torch.cuda.synchronize()
+        assert int(st.item()) == 4
+        sph.sph_radial_expansion(xyz, torch.tensor(bad, device="cuda"), Rt, L, True, status=st.fill_(-1))
         torch.cuda.synchronize()
         assert int(st.item()) == 4
