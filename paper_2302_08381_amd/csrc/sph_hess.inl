@@ -3,256 +3,281 @@
 // Cartesian recursion gives derivatives of any order by applying Eq.
 // iter-deri again).
 //
-// Mapping: a 16-point tile per block, four lanes per point.  Lane (p, a)
-// forms row a of the Hessian of every column of point p, i.e. the
-// Hessian-vector product H_k e_a, with the same algebra as the double
-// backward:
-//   H(Qt) v = ( Tm vx + x W, Tm vy + y W, W1 rho + W0 vz ),
-//     rho = x vx + y vy,  W = W2 rho + W1 vz,
-//     Tm = gxy Qt_{l-1}^{m+1}, W2 = h2 Qt_{l-2}^{m+2}, W1 = h1 Qt_{l-2}^{m+1},
-//     W0 = h0 Qt_{l-2}^m,
-// the product rule with the order-m factor t = c_m or s_m
-//   H(Qt t) v = t H(Qt) v + grad Qt (grad t . v) + grad t (grad Qt . v)
-//               + Qt H(t) v,
-// and, for the normalised harmonics Y(x) = Yt(u), u = x/r,
-//   H Y v = [ H Yt v - l (g (u.v) + u (g.v)) - l Yt v + l(l+2) Yt u (u.v) ] / r^2
-// with g = grad Yt(u).  The fourth lane of each point has no row (v = 0) and
-// only helps with the stores.  Rows go into an LDS tile laid out like the
-// global block [16 points][3][3][K], so the tile leaves as contiguous 16-byte
-// stores.  Where the nine rows of a point exceed the per-point budget the
-// degrees are taken in groups and each group's partial rows are stored.
+// Mapping: one lane per (point, order), or two, one per sign of the order, in
+// waves of their own.  A lane walks the degrees l = m .. l_max upward at fixed
+// order with the recursion of OrdChain carried one derivative further:
+// p_l = Qt_l^m / N_l^m, e = 2 dp/d(rho^2), w = 2 de/d(rho^2), and along z
+// dp_l/dz = (l-m) p_{l-1}.  With T = N e, W = N w, V = N (l-m) e_{l-1},
+// U = N (l-m)(l-1-m) p_{l-2},
+//   H(Qt) = [ T + x^2 W   x y W       x V ]
+//           [             T + y^2 W   y V ]
+//           [                         U   ]
+// and with the order's factor t = c_m or s_m the six unique entries of a
+// column are
+//   H(Qt t) = t H(Qt) + grad Qt grad t' + grad t grad Qt' + Qt H(t).
+// For the normalised harmonics Y(x) = Yt(u), u = x / r, with g = grad Yt(u),
+//   H Y = [ H Yt - l (u s' + s u') - l Yt 1 ] / r^2,  s = g - (l+2)/2 Yt u.
+// The entries go into an LDS tile laid out like the global block
+// [points][3][3][K] and leave as 16-byte stores.
+//
+// The tile decides how many points a CU holds at once (1.8 KB each at l_max 6
+// in float), so the orders and signs are what fills its waves; a lane per row
+// of the 3x3 block forms each off-diagonal entry twice and the shared factors
+// three times (VALU 85 % busy).  Measured against that, 1e6 points: float
+// l_max 3 124 -> 100 us, l_max 6 392 -> 308 (5.7 TB/s of stores), l_max 8
+// (500 000) 511 -> 260, l_max 12 (300 000) 1242 -> 359; double l_max 4 (500
+// 000) 192 -> 158, l_max 8 (300 000) 827 -> 312; l_max 32 float (30 000) 1395
+// -> 415, double (10 000) 1156 -> 326.  What is left is the stores up to l_max
+// 8; past it the few waves that the tile leaves.  Error against double, float
+// l_max 6 / 12: 5e-7 / 6e-7 of a point's largest entry (1.6e-6 / 2e-6).
 #pragma once
 
-#include "sph_device.hpp"
-#include "sph_launch.hpp"
+#include "sph_ord.inl"
 
 namespace sph {
 
-constexpr int kHessPoints = 16;  // points per tile (four lanes each)
-
-// Per-point LDS budget of one of the nine rows (elements): one group of
-// degrees up to l_max = 8 (float) or 5 (double), a tile of about 47 KB.
+// LDS elements of a tile of `points` Hessians.  A point's nine rows take a
+// stride that is padded by one 16-byte vector where it would be a multiple of
+// 16 banks (odd l_max), so that the lanes of one order hit distinct ones.
 template <typename T>
-inline constexpr int kHessBudget = 86;
-template <>
-inline constexpr int kHessBudget<double> = 43;
-
-// Degrees [la, lb) of one point's Hessian row a (v = e_a; v = 0 for the lane
-// without a row) into the LDS rows at `out` (three rows of stride S, column
-// k at out[k - kb]).
-template <typename T, int MM, bool NORM>
-__device__ __forceinline__ void hess_rows(const Point<T>& pt, T vx, T vy, T vz, bool has_row, int la,
-                                          int lb, int kb, int S, T* out) {
-  const CoefTable<T>& C = coef<T>();
-  constexpr T kIS2 = T(kInvSqrt2d);
-  const T ex = pt.ex, ey = pt.ey, ez = pt.ez;
-  const T rho = ex * vx + ey * vy;
-  const T uv = rho + ez * vz;  // u . v (normalised: ex = u)
-  const T ir2 = pt.inv_r * pt.inv_r;
-  // order-m terms tabulated once per point (buckets up to m = 12):
-  //   c_m, s_m;  m c_{m-1}, m s_{m-1};  grad(c_m).v, grad(s_m).v;
-  //   hA, hB with H(c_m) v = (hA, -hB), H(s_m) v = (hB, hA)
-  constexpr bool kTab = MM <= 12;
-  constexpr int MT = kTab ? MM + 1 : 1;
-  T tc[MT], ts[MT], tmc[MT], tms[MT], tvc[MT], tvs[MT], thA[MT], thB[MT];
-  if constexpr (kTab) {
-    T s2 = T(0), c2 = T(0), s1 = T(0), c1 = T(1), s0 = T(0), c0 = T(1);
-#pragma unroll
-    for (int m = 0; m <= MM; ++m) {
-      if (m > 0) {
-        const T sn = ex * s0 + ey * c0;
-        const T cn = ex * c0 - ey * s0;
-        s2 = s1;
-        c2 = c1;
-        s1 = s0;
-        c1 = c0;
-        s0 = sn;
-        c0 = cn;
-      }
-      const T fm = T(m), fmm = T(m * (m - 1));
-      tc[m] = c0;
-      ts[m] = s0;
-      tmc[m] = fm * c1;
-      tms[m] = fm * s1;
-      tvc[m] = tmc[m] * vx - tms[m] * vy;
-      tvs[m] = tms[m] * vx + tmc[m] * vy;
-      thA[m] = fmm * (c2 * vx - s2 * vy);
-      thB[m] = fmm * (s2 * vx + c2 * vy);
-    }
-  }
-  T pp[MM + 3], prev[MM + 3], cur[MM + 3];
-  q_row_rt<T, MM>(la - 2, ez, pt.rxy2, pp);
-  q_row_rt<T, MM>(la - 1, ez, pt.rxy2, prev);
-  T* row = out - kb;
-#pragma unroll 1
-  for (int l = la; l < lb; ++l) {
-    q_row_rt<T, MM>(l, ez, pt.rxy2, cur);
-    const int k0 = l * l + l;
-    // normalised: H Y v = [h - l (g (u.v) + u (g.v)) - l Yt v + l(l+2) Yt u (u.v)] / r^2
-    //                   = [h - luv g - lu (g.v) - bv Yt] / r^2 per component,
-    // with the degree's luv = l (u.v), lu = l u, bv = l v - l(l+2) (u.v) u
-    T luv = T(0), lux = T(0), luy = T(0), luz = T(0), bx = T(0), by = T(0), bz = T(0);
-    if constexpr (NORM) {
-      const T fl = T(l), A = T(l) * T(l + 2) * uv;
-      luv = fl * uv;
-      lux = fl * ex;
-      luy = fl * ey;
-      luz = fl * ez;
-      bx = fl * vx - A * ex;
-      by = fl * vy - A * ey;
-      bz = fl * vz - A * ez;
-    }
-    // Yt, g = grad Yt, gv = g.v, h = H(Yt) v of column k
-    auto put = [&](int k, T Yt, T gx, T gy, T gz, T gv, T hx, T hy, T hz) {
-      if constexpr (NORM) {
-        hx = (hx - luv * gx - lux * gv - bx * Yt) * ir2;
-        hy = (hy - luv * gy - luy * gv - by * Yt) * ir2;
-        hz = (hz - luv * gz - luz * gv - bz * Yt) * ir2;
-      }
-      if (has_row) {
-        row[k] = hx;
-        row[S + k] = hy;
-        row[2 * S + k] = hz;
-      }
-    };
-    T s2 = T(0), c2 = T(0);  // s_{m-2}, c_{m-2}
-    T s1 = T(0), c1 = T(1);  // s_{m-1}, c_{m-1}
-    T s0 = T(0), c0 = T(1);  // s_m, c_m
-#pragma unroll
-    for (int m = 0; m <= MM; ++m) {
-      if (m > l) continue;  // no early exit: keeps the loop fully unrolled
-      if (!kTab && m > 0) {
-        const T sn = ex * s0 + ey * c0;
-        const T cn = ex * c0 - ey * s0;
-        s2 = s1;
-        c2 = c1;
-        s1 = s0;
-        c1 = c0;
-        s0 = sn;
-        c0 = cn;
-      }
-      const T q = cur[m];
-      const T Tm = (m <= l - 2) ? C.gxy[l][m] * prev[m + 1] : T(0);
-      const T Cz = (m <= l - 1) ? C.gz[l][m] * prev[m] : T(0);
-      const T W2 = (m <= l - 4) ? C.h2[l][m] * pp[m + 2] : T(0);
-      const T W1 = (m <= l - 3) ? C.h1[l][m] * pp[m + 1] : T(0);
-      const T W0 = (m <= l - 2) ? C.h0[l][m] * pp[m] : T(0);
-      const T Qx = ex * Tm, Qy = ey * Tm;  // grad Qt = (Qx, Qy, Cz)
-      const T W = W2 * rho + W1 * vz;
-      const T Hx = Tm * vx + ex * W;  // H(Qt) v
-      const T Hy = Tm * vy + ey * W;
-      const T Hz = W1 * rho + W0 * vz;
-      const T gQv = Tm * rho + Cz * vz;  // grad Qt . v
-      if (m == 0) {
-        put(k0, q * kIS2, Qx * kIS2, Qy * kIS2, Cz * kIS2, gQv * kIS2, Hx * kIS2, Hy * kIS2, Hz * kIS2);
-      } else {
-        T c, sm, mc, ms, tvp, tvm, hA, hB;
-        if constexpr (kTab) {
-          const int mt = kTab ? m : 0;
-          c = tc[mt];
-          sm = ts[mt];
-          mc = tmc[mt];
-          ms = tms[mt];
-          tvp = tvc[mt];
-          tvm = tvs[mt];
-          hA = thA[mt];
-          hB = thB[mt];
-        } else {
-          const T fm = T(m), fmm = T(m * (m - 1));
-          c = c0;
-          sm = s0;
-          mc = fm * c1;
-          ms = fm * s1;
-          tvp = mc * vx - ms * vy;
-          tvm = ms * vx + mc * vy;
-          hA = fmm * (c2 * vx - s2 * vy);
-          hB = fmm * (s2 * vx + c2 * vy);
-        }
-        {  // +m: t = c_m, grad t = (mc, -ms, 0), H(t) v = (hA, -hB, 0)
-          const T gx = c * Qx + q * mc;
-          const T gy = c * Qy - q * ms;
-          const T gz = c * Cz;
-          const T gv = c * gQv + q * tvp;
-          const T hx = c * Hx + Qx * tvp + mc * gQv + q * hA;
-          const T hy = c * Hy + Qy * tvp - ms * gQv - q * hB;
-          const T hz = c * Hz + Cz * tvp;
-          put(k0 + m, q * c, gx, gy, gz, gv, hx, hy, hz);
-        }
-        {  // -m: t = s_m, grad t = (ms, mc, 0), H(t) v = (hB, hA, 0)
-          const T gx = sm * Qx + q * ms;
-          const T gy = sm * Qy + q * mc;
-          const T gz = sm * Cz;
-          const T gv = sm * gQv + q * tvm;
-          const T hx = sm * Hx + Qx * tvm + ms * gQv + q * hB;
-          const T hy = sm * Hy + Qy * tvm + mc * gQv + q * hA;
-          const T hz = sm * Hz + Cz * tvm;
-          put(k0 - m, q * sm, gx, gy, gz, gv, hx, hy, hz);
-        }
-      }
-    }
-    copy_row<T, MM>(MM, prev, pp);
-    copy_row<T, MM>(MM, cur, prev);
-  }
+__host__ __device__ constexpr int hess_pad(int L) {
+  return (L & 1) != 0 ? 16 / static_cast<int>(sizeof(T)) : 0;
+}
+template <typename T>
+__host__ __device__ constexpr size_t hess_lds_bytes(int L, int points) {
+  return sizeof(T) * static_cast<size_t>(ord_block<T>(points * (9 * (L + 1) * (L + 1) + hess_pad<T>(L))));
 }
 
-// MM: m-extent bucket (l_max <= MM).  DS = 2 (one group of degrees only): a
-// block of two waves on the tile, wave h forming degrees [0, LS) or
-// [LS, l_max] (LS balances the columns; the branch is uniform per wave), both
-// waves storing the tile.  Dynamic LDS: 16 * 9 * stride elements.
-template <typename T, int MM, bool NORM, int DS>
-__global__ __launch_bounds__(kWave * DS) void k_hess(HessParams P) {
-  constexpr int B = kHessBudget<T>;
-  constexpr int NT = kWave * DS;
-  constexpr int PT = kHessPoints;
+// Waves per order (one, or two for the two signs) and points per tile: the
+// signs apart from l_max 6 (float l_max 5 255 us against 223 together, l_max 6
+// 308 and 310, l_max 8 260 and 270, l_max 12 359 and 406); the most points of
+// one wave, or two with the signs apart, whose tile leaves three blocks in a
+// CU's LDS and whose lanes fill three quarters of their waves (float l_max 6
+// 18 points 308 us, 14 339; l_max 12 8 points 359, 9 408 and 4 397; double
+// l_max 7 8 points 242, 11 283); where no number does, the most that fit.
+constexpr int hess_split(int L) { return L >= 6 ? 2 : 1; }
+template <typename T>
+constexpr int hess_points(int L) {
+  const int lanes = 64 * hess_split(L);
+  int most = 1;
+  for (int p = 2; p * (L + 1) <= lanes && hess_lds_bytes<T>(L, p) <= 53 * 1024; ++p) most = p;
+  for (int p = most; p >= 1; --p) {
+    const int used = p * (L + 1);
+    if (4 * used >= 3 * ((used + 63) / 64 * 64)) return p;
+  }
+  return most;
+}
+
+// LT: l_max at compile time, or -1 (P.L).  P.tile points per block; SP waves
+// per order of P.tile (l_max + 1) lanes, rounded up to whole waves.  Dynamic
+// LDS: hess_lds_bytes.  A grid-stride loop over tiles, so any grid is correct.
+template <typename T, int LT, bool NORM, int SP>
+__global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
+  constexpr T kIS2 = T(kInvSqrt2d);
+  constexpr int W = Vec16<T>::n;
   extern __shared__ __align__(16) unsigned char smem[];
   T* st = reinterpret_cast<T*>(smem);
-  const int tid = threadIdx.x;
-  const int lane = tid % kWave;
-  const int half = tid / kWave;
-  const int p = lane / 4, a = lane % 4;
-  const int L = P.L;
-  const int K = (L + 1) * (L + 1);
-  const T vx = a == 0 ? T(1) : T(0), vy = a == 1 ? T(1) : T(0), vz = a == 2 ? T(1) : T(0);
-  T* d2 = static_cast<T*>(P.d2Y);
-  const int64_t ntiles = (P.n + PT - 1) / PT;
-  for (int64_t tile = xcd_slot(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
+  const int L = LT >= 0 ? LT : P.L;
+  const int K = (L + 1) * (L + 1), R9 = 9 * K;
+  const int pad = hess_pad<T>(L), S9 = R9 + pad;
+  const int PT = P.tile;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const OrdTable<T>& C = ord_table<T>(0);
+  const int half = SP == 2 ? nt / 2 : nt;  // whole waves
+  const int part = SP == 2 ? __builtin_amdgcn_readfirstlane(tid / half) : 0;
+  const int it = tid - part * half;
+  const int m = it / PT, p = it - m * PT;
+  const bool lane_on = m <= L && !(part == 1 && m == 0);
+  const int mm = m <= L ? m : L;
+  const int lw = __builtin_amdgcn_readfirstlane(it / kWave * kWave / PT);
+  const int l0 = lw <= L ? lw : L + 1;
+  const int64_t tiles = (P.n + PT - 1) / PT;
+  for (int64_t tile = xcd_slot(blockIdx.x, gridDim.x); tile < tiles; tile += gridDim.x) {
     const int64_t p0 = tile * PT;
     const int np = static_cast<int>(P.n - p0 < PT ? P.n - p0 : PT);
-    T x = T(0), y = T(0), z = T(0);
-    if (p < np) {
-      const T* q = static_cast<const T*>(P.xyz) + (p0 + p) * 3;
-      x = q[0];
-      y = q[1];
-      z = q[2];
+    const T* xp = static_cast<const T*>(P.xyz) + (p0 + (p < np ? p : np - 1)) * 3;
+    const Point<T> pt = make_point<T, NORM>(xp[0], xp[1], xp[2]);
+    T* gd = static_cast<T*>(P.d2Y) + p0 * R9;
+    const int sh = ord_shift(gd);
+    // the evaluation point and its powers in double, as in k_ord
+    double ux = xp[0], uy = xp[1], uz = xp[2], ui = 1.0;
+    if constexpr (NORM) {
+      ui = static_cast<double>(pt.inv_r);
+      if constexpr (!std::is_same_v<T, double>) {
+        const double rr = ux * ux + uy * uy + uz * uz;
+        ui = pt.inv_r == T(0) ? 0.0 : ui * (1.5 - 0.5 * rr * ui * ui);
+      }
+      ux *= ui;
+      uy *= ui;
+      uz *= ui;
     }
-    const Point<T> pt = make_point<T, NORM>(x, y, z);
-    const bool has_row = a < 3 && p < np;
-    T* dst = d2 + p0 * 9 * K;
-    if constexpr (DS == 2) {
-      const int S = row_stride<T>(K, true);
-      int LS = 1;  // smallest degree with LS^2 >= K / 2
-      while (LS <= L && 2 * LS * LS < K) ++LS;
-      T* out = st + (p * 9 + a * 3) * S;
-      if (half == 0)
-        hess_rows<T, MM, NORM>(pt, vx, vy, vz, has_row, 0, LS, 0, S, out);
-      else
-        hess_rows<T, MM, NORM>(pt, vx, vy, vz, has_row, LS, L + 1, 0, S, out);
-      __syncthreads();
-      copy_out<NT>(st, S, dst, K, K, np * 9, tid, aligned16(dst));
-      __syncthreads();
-    } else {
-      for (int la = 0; la <= L;) {
-        const int lb = group_end(la, L, B);
-        const int kb = la * la;
-        const int cnt = lb * lb - kb;
-        const int S = row_stride<T>(cnt, cnt == K);
-        hess_rows<T, MM, NORM>(pt, vx, vy, vz, has_row, la, lb, kb, S, st + (p * 9 + a * 3) * S);
-        __syncthreads();
-        copy_out(st, S, dst + kb, K, cnt, np * 9, lane, aligned16(dst + kb));
-        __syncthreads();
-        la = lb;
+    // (x + i y)^(m-2) by squaring, then two more factors
+    constexpr int kBits = LT < 0 ? 5 : (LT > 9 ? 4 : (LT > 5 ? 3 : (LT > 3 ? 2 : 1)));
+    double c2 = 1.0, s2 = 0.0;
+    {
+      const int ex = mm >= 2 ? mm - 2 : 0;
+      double bc = ux, bs = uy;
+#pragma unroll
+      for (int b = 0; b < kBits; ++b) {
+        if ((ex >> b) & 1) {
+          const double t = c2 * bc - s2 * bs;
+          s2 = c2 * bs + s2 * bc;
+          c2 = t;
+        }
+        const double t = bc * bc - bs * bs;
+        bs = 2.0 * bc * bs;
+        bc = t;
       }
     }
+    double c1 = 1.0, s1 = 0.0;
+    if (mm >= 2) {
+      c1 = c2 * ux - s2 * uy;
+      s1 = c2 * uy + s2 * ux;
+    }
+    const double c0 = c1 * ux - s1 * uy, s0 = c1 * uy + s1 * ux;
+    const double fm = mm, fmm = mm * (mm - 1);
+    // the order's factor t, its gradient and its second derivatives xx and xy
+    // (yy = -xx), for the columns +m (c_m) and -m (s_m)
+    T tp = static_cast<T>(c0), tpx = static_cast<T>(fm * c1), tpy = static_cast<T>(-fm * s1);
+    T tpA = static_cast<T>(fmm * c2), tpB = static_cast<T>(-fmm * s2);
+    T tm = static_cast<T>(s0), tmx = static_cast<T>(fm * s1), tmy = static_cast<T>(fm * c1);
+    T tmA = static_cast<T>(fmm * s2), tmB = static_cast<T>(fmm * c2);
+    if (mm == 0) {  // one column: both signs write the same values
+      tp = tm = kIS2;
+      tpx = tpy = tmx = tmy = T(0);
+    }
+    if constexpr (SP == 2) {
+      if (part == 1) {
+        tp = tm;
+        tpx = tmx;
+        tpy = tmy;
+        tpA = tmA;
+        tpB = tmB;
+      }
+    }
+    const T x = static_cast<T>(ux), y = static_cast<T>(uy), z = static_cast<T>(uz);
+    const T ir2 = static_cast<T>(ui * ui);
+    const T rho2 = static_cast<T>(ux * ux + uy * uy);
+    // fx = l - m; p1, p2, e1, w1: the degrees below; d, f, g: see OrdChain
+    T fx = T(0), pv = T(1), p1 = T(0), p2 = T(0), d = T(0), e = T(0), e1 = T(0), f = T(0), w = T(0), w1 = T(0), g = T(0);
+    T* base = st + sh + p * S9 + l0 * l0 + l0 + (SP == 2 && part == 1 ? -mm : mm);
+    T* basm = base - 2 * mm;
+    T fl = T(l0);
+    auto degree = [&](int l, T N, T inv) {
+      if (lane_on && l >= mm) {
+        if constexpr (NORM) N *= ir2;
+        const T q = N * pv, Tm = N * e, Wn = N * w;
+        const T Nx = N * fx;
+        const T Z = Nx * p1, V = Nx * e1, U = Nx * ((fx - T(1)) * p2);
+        const T Qx = x * Tm, Qy = y * Tm;
+        const T xW = x * Wn;
+        const T Qxx = x * xW + Tm, Qxy = y * xW, Qyy = y * (y * Wn) + Tm;
+        const T Qxz = x * V, Qyz = y * V;
+        const T lx = fl * x, ly = fl * y, lz = fl * z;
+        const T hl = (T(0.5) * fl + T(1)) * q;  // (l + 2)/2 q
+        auto col = [&](T* o, T t, T tx, T ty, T A, T B) {
+          T hxx = Qxx * t + (T(2) * Qx * tx + q * A);
+          T hyy = Qyy * t + (T(2) * Qy * ty - q * A);
+          T hxy = Qxy * t + (Qx * ty + (Qy * tx + q * B));
+          T hxz = Qxz * t + Z * tx;
+          T hyz = Qyz * t + Z * ty;
+          T hzz = U * t;
+          if constexpr (NORM) {
+            const T h = hl * t;
+            const T sx = Qx * t + (q * tx - h * x);
+            const T sy = Qy * t + (q * ty - h * y);
+            const T sz = Z * t - h * z;
+            const T ly0 = fl * (q * t);
+            hxx -= T(2) * (lx * sx) + ly0;
+            hyy -= T(2) * (ly * sy) + ly0;
+            hzz -= T(2) * (lz * sz) + ly0;
+            hxy -= lx * sy + ly * sx;
+            hxz -= lx * sz + lz * sx;
+            hyz -= ly * sz + lz * sy;
+          }
+          o[0] = hxx;
+          o[K] = hxy;
+          o[2 * K] = hxz;
+          o[3 * K] = hxy;
+          o[4 * K] = hyy;
+          o[5 * K] = hyz;
+          o[6 * K] = hxz;
+          o[7 * K] = hyz;
+          o[8 * K] = hzz;
+        };
+        col(base, tp, tpx, tpy, tpA, tpB);
+        if constexpr (SP == 1) col(basm, tm, tmx, tmy, tmA, tmB);
+        // one degree up
+        const T a = fx * inv;
+        g = a * (z * g - (rho2 * w1 + T(4) * e1));
+        w1 = w;
+        w = z * w + g;
+        f = a * (z * f - (rho2 * e1 + T(2) * p1));
+        e1 = e;
+        e = z * e + f;
+        d = a * (z * d - rho2 * p1);
+        p2 = p1;
+        p1 = pv;
+        pv = z * pv + d;
+        fx += T(1);
+      }
+      fl += T(1);
+      base += 2 * l + 2;
+      basm += 2 * l + 2;
+    };
+    T Ac[2 * kOrdStep], Bc[2 * kOrdStep];
+#pragma unroll
+    for (int u = 0; u < kOrdStep; ++u) {
+      Ac[2 * u] = C.a[l0 + u][2 * mm];
+      Ac[2 * u + 1] = C.a[l0 + u][2 * mm + 1];
+    }
+#pragma unroll 1
+    for (int l = l0; l <= L; l += kOrdStep) {
+#pragma unroll
+      for (int u = 0; u < kOrdStep; ++u) {
+        Bc[2 * u] = C.a[l + kOrdStep + u][2 * mm];
+        Bc[2 * u + 1] = C.a[l + kOrdStep + u][2 * mm + 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kOrdStep; ++u) {
+        if (l + u <= L) degree(l + u, Ac[2 * u], u + 1 < kOrdStep ? Ac[(2 * u + 3) % (2 * kOrdStep)] : Bc[1]);
+        // one degree after the other: interleaved they take more registers
+        asm volatile("" : "+v"(pv), "+v"(p1), "+v"(e), "+v"(w));
+      }
+#pragma unroll
+      for (int u = 0; u < 2 * kOrdStep; ++u) Ac[u] = Bc[u];
+    }
+    __syncthreads();
+    const int cnt = np * R9;
+    if (pad == 0) {
+      ord_copy_out(st, sh, gd, cnt, tid, nt);
+    } else if (sh == 0) {  // points of whole vectors, one between them; as ord_copy_out
+      using V = typename Vec16<T>::type;
+      const int rv = R9 / W, nv = np * rv;
+      const __amdgpu_buffer_rsrc_t rs = stream_rsrc(gd, nv * 16);
+      V* gv = reinterpret_cast<V*>(gd);
+      const V* sv = reinterpret_cast<const V*>(st);
+      constexpr int kLine = 128 / 16;
+      int v0 = (kLine - static_cast<int>((reinterpret_cast<uintptr_t>(gv) / 16) % kLine)) % kLine;
+      v0 = v0 < nv ? v0 : nv;
+      const int v1 = v0 + (nv - v0) / kLine * kLine;
+      for (int i0 = v0 + tid; i0 < v1; i0 += nt * kOrdBatch) {
+        V v[kOrdBatch];
+#pragma unroll
+        for (int u = 0; u < kOrdBatch; ++u) {
+          const int i = i0 + u * nt;
+          if (i < v1) v[u] = sv[i + i / rv];
+        }
+#pragma unroll
+        for (int u = 0; u < kOrdBatch; ++u)
+          if (i0 + u * nt < v1) stream_store16(v[u], rs, (i0 + u * nt) * 16);
+      }
+      if (tid < v0) gv[tid] = sv[tid + tid / rv];
+      if (tid < nv - v1) gv[v1 + tid] = sv[v1 + tid + (v1 + tid) / rv];
+    } else {
+      for (int i = tid; i < cnt; i += nt) gd[i] = st[sh + i + i / R9 * pad];
+    }
+    if (tile + gridDim.x < tiles) __syncthreads();
   }
 }
 

@@ -57,6 +57,7 @@ struct HessParams {
   int64_t n;
   int32_t L;
   void* d2Y;        // [n,3,3,K]
+  int32_t tile;     // points per block
 };
 
 // Radial expansion over CSR environments (k_expand).
@@ -248,9 +249,8 @@ KernelInfo bwd_info_f32(int L);
 KernelInfo bwd_info_f64(int L);
 KernelInfo dbwd_info_f32(int L, int normalize);
 KernelInfo dbwd_info_f64(int L, int normalize);
-// Explicit Hessians: the run-time-degree kernel of the m-extent bucket of L,
-// with a two-wave degree-split block where the nine rows of a point fit one
-// group of degrees; tile_points = 16.
+// Explicit Hessians: k_hess with L at compile time up to kCompileMax, else the
+// run-time one; tile_points points per block.
 KernelInfo hess_info_f32(int L, int normalize);
 KernelInfo hess_info_f64(int L, int normalize);
 // Radial expansion: k_expfwd where it serves (lds_bytes set; aligned: R starts
