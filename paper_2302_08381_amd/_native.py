@@ -107,11 +107,30 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _public_stream(index: int) -> int:
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# The current stream's handle without a torch.cuda.Stream object (0.1 us
+# instead of 2.1); builds of torch without it take the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _public_stream)
+
+
+def _call(device, fn, *args):
+    """fn(*args, stream) on torch's current stream of ``device``, which is made
+    the current device unless it is already (the context manager is 1.3 us of
+    a call of 8); raises SphError on a non-zero status."""
+    index = device.index
+    if index is not None and index == torch.cuda.current_device():
+        status = fn(*args, _raw_stream(index))
+    else:
+        with torch.cuda.device(device):
+            status = fn(*args, _raw_stream(index))
+    if status != SPH_OK:
+        _check(status)
 
 
 def _need(t: torch.Tensor, name: str, shape, dtype, device):
@@ -129,7 +148,7 @@ def _need(t: torch.Tensor, name: str, shape, dtype, device):
 def _check_xyz(xyz: torch.Tensor):
     if not isinstance(xyz, torch.Tensor) or xyz.dim() != 2 or xyz.shape[1] != 3:
         raise ValueError("xyz must be a [n,3] tensor")
-    if xyz.device.type != "cuda":
+    if not xyz.is_cuda:
         raise ValueError("xyz must be on a HIP device")
     if not xyz.is_contiguous():
         raise ValueError("xyz must be contiguous")
@@ -180,9 +199,7 @@ def sph_compute(xyz: torch.Tensor, l_max: int, normalize: bool = True, Y: torch.
         Y = torch.empty((n, max(K, 0)), dtype=xyz.dtype, device=xyz.device)
     else:
         _need(Y, "Y", (n, K), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_compute(_ptr(xyz), n, int(l_max), int(bool(normalize)), _dtype_code(xyz),
-                                 _ptr(Y), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_compute, _ptr(xyz), n, int(l_max), int(bool(normalize)), _dtype_code(xyz), _ptr(Y))
     return Y
 
 
@@ -200,9 +217,8 @@ def sph_compute_with_gradients(xyz: torch.Tensor, l_max: int, normalize: bool = 
         dY = torch.empty((n, 3, K), dtype=xyz.dtype, device=xyz.device)
     else:
         _need(dY, "dY", (n, 3, K), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_compute_with_gradients(_ptr(xyz), n, int(l_max), int(bool(normalize)),
-                                                _dtype_code(xyz), _ptr(Y), _ptr(dY), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_compute_with_gradients, _ptr(xyz), n, int(l_max), int(bool(normalize)),
+          _dtype_code(xyz), _ptr(Y), _ptr(dY))
     return Y, dY
 
 
@@ -218,8 +234,7 @@ def sph_e3nn_coordinates(xyz: torch.Tensor, out: torch.Tensor | None = None) -> 
         out = torch.empty_like(xyz)
     else:
         _need(out, "out", (n, 3), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_e3nn_coordinates(_ptr(xyz), n, _dtype_code(xyz), _ptr(out), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_e3nn_coordinates, _ptr(xyz), n, _dtype_code(xyz), _ptr(out))
     return out
 
 
@@ -233,9 +248,8 @@ def sph_e3nn_convert(Y: torch.Tensor, dY: torch.Tensor | None, l_max: int, norma
     _need(Y, "Y", (n, K), Y.dtype, Y.device)
     if dY is not None:
         _need(dY, "dY", (n, 3, K), Y.dtype, Y.device)
-    with torch.cuda.device(Y.device):
-        _check(lib().sph_e3nn_convert(n, int(l_max), E3NN_NORMALIZATIONS[normalization], _dtype_code(Y), _ptr(Y),
-                                      _ptr(dY), _stream(Y.device)))
+    _call(Y.device, lib().sph_e3nn_convert, n, int(l_max), E3NN_NORMALIZATIONS[normalization], _dtype_code(Y),
+          _ptr(Y), _ptr(dY))
     return Y, dY
 
 
@@ -247,10 +261,8 @@ def sph_e3nn_compute(xyz_p: torch.Tensor, l_max: int, normalize: bool = True, no
     n = xyz_p.shape[0]
     K = (int(l_max) + 1) ** 2 if l_max >= 0 else 0
     Y = torch.empty((n, K), dtype=xyz_p.dtype, device=xyz_p.device)
-    with torch.cuda.device(xyz_p.device):
-        _check(lib().sph_e3nn_compute(_ptr(xyz_p), n, int(l_max), int(bool(normalize)),
-                                      E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p), _ptr(Y),
-                                      _stream(xyz_p.device)))
+    _call(xyz_p.device, lib().sph_e3nn_compute, _ptr(xyz_p), n, int(l_max), int(bool(normalize)),
+          E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p), _ptr(Y))
     return Y
 
 
@@ -264,10 +276,8 @@ def sph_e3nn_vector_jacobian(xyz_p: torch.Tensor, grad_Y: torch.Tensor, l_max: i
     n = xyz_p.shape[0]
     _need(grad_Y, "grad_Y", (n, (int(l_max) + 1) ** 2), xyz_p.dtype, xyz_p.device)
     grad_xyz = torch.empty((n, 3), dtype=xyz_p.dtype, device=xyz_p.device)
-    with torch.cuda.device(xyz_p.device):
-        _check(lib().sph_e3nn_vector_jacobian(_ptr(xyz_p), _ptr(grad_Y), n, int(l_max), int(bool(normalize)),
-                                              E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p),
-                                              _ptr(grad_xyz), _stream(xyz_p.device)))
+    _call(xyz_p.device, lib().sph_e3nn_vector_jacobian, _ptr(xyz_p), _ptr(grad_Y), n, int(l_max),
+          int(bool(normalize)), E3NN_NORMALIZATIONS[normalization], _dtype_code(xyz_p), _ptr(grad_xyz))
     return grad_xyz
 
 
@@ -293,9 +303,8 @@ def sph_compute_with_hessians(xyz: torch.Tensor, l_max: int, normalize: bool = T
         d2Y = torch.empty((n, 3, 3, K), dtype=xyz.dtype, device=xyz.device)
     else:
         _need(d2Y, "d2Y", (n, 3, 3, K), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_compute_with_hessians(_ptr(xyz), n, int(l_max), int(bool(normalize)), _dtype_code(xyz),
-                                               _ptr(Y), _ptr(dY), _ptr(d2Y), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_compute_with_hessians, _ptr(xyz), n, int(l_max), int(bool(normalize)),
+          _dtype_code(xyz), _ptr(Y), _ptr(dY), _ptr(d2Y))
     return Y, dY, d2Y
 
 
@@ -309,9 +318,7 @@ def sph_backward(dY: torch.Tensor, grad_Y: torch.Tensor, l_max: int, grad_xyz: t
         grad_xyz = torch.empty((n, 3), dtype=dY.dtype, device=dY.device)
     else:
         _need(grad_xyz, "grad_xyz", (n, 3), dY.dtype, dY.device)
-    with torch.cuda.device(dY.device):
-        _check(lib().sph_backward(_ptr(dY), _ptr(grad_Y), n, int(l_max), _dtype_code(dY), _ptr(grad_xyz),
-                                  _stream(dY.device)))
+    _call(dY.device, lib().sph_backward, _ptr(dY), _ptr(grad_Y), n, int(l_max), _dtype_code(dY), _ptr(grad_xyz))
     return grad_xyz
 
 
@@ -327,9 +334,8 @@ def sph_vector_jacobian(xyz: torch.Tensor, grad_Y: torch.Tensor, l_max: int, nor
         grad_xyz = torch.empty((n, 3), dtype=xyz.dtype, device=xyz.device)
     else:
         _need(grad_xyz, "grad_xyz", (n, 3), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_vector_jacobian(_ptr(xyz), _ptr(grad_Y), n, int(l_max), int(bool(normalize)),
-                                         _dtype_code(xyz), _ptr(grad_xyz), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_vector_jacobian, _ptr(xyz), _ptr(grad_Y), n, int(l_max), int(bool(normalize)),
+          _dtype_code(xyz), _ptr(grad_xyz))
     return grad_xyz
 
 
@@ -350,10 +356,8 @@ def sph_double_backward(xyz: torch.Tensor, grad_Y: torch.Tensor, v: torch.Tensor
     if want_grad_xyz:
         g2 = torch.empty((n, 3), dtype=xyz.dtype, device=xyz.device) if grad_xyz2 is None else \
             _need(grad_xyz2, "grad_xyz2", (n, 3), xyz.dtype, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_double_backward(_ptr(xyz), _ptr(grad_Y), _ptr(v), n, int(l_max),
-                                         int(bool(normalize)), _dtype_code(xyz), _ptr(ggY), _ptr(g2),
-                                         _stream(xyz.device)))
+    _call(xyz.device, lib().sph_double_backward, _ptr(xyz), _ptr(grad_Y), _ptr(v), n, int(l_max),
+          int(bool(normalize)), _dtype_code(xyz), _ptr(ggY), _ptr(g2))
     return ggY, g2
 
 
@@ -397,10 +401,8 @@ def sph_batched_compute(xyz: torch.Tensor, offsets: torch.Tensor, l_max: int, no
         gx = torch.empty((n, 3), dtype=xyz.dtype, device=xyz.device) if gx is None else \
             _need(gx, "grad_xyz", (n, 3), xyz.dtype, xyz.device)
     status, check = _csr_status(status, check, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_batched_compute(_ptr(xyz), _ptr(offsets), n_env, n, int(l_max), int(bool(normalize)),
-                                         _dtype_code(xyz), _ptr(Y), _ptr(dY), _ptr(grad_Y), _ptr(gx),
-                                         _ptr(status), _stream(xyz.device)))
+    _call(xyz.device, lib().sph_batched_compute, _ptr(xyz), _ptr(offsets), n_env, n, int(l_max), int(bool(normalize)),
+          _dtype_code(xyz), _ptr(Y), _ptr(dY), _ptr(grad_Y), _ptr(gx), _ptr(status))
     _raise_on_status(status, check)
     return {"Y": Y, "dY": dY, "grad_xyz": gx, "status": status}
 
@@ -427,10 +429,8 @@ def sph_radial_expansion(xyz: torch.Tensor, offsets: torch.Tensor, R: torch.Tens
     c = torch.empty((n_env, n_max, K), dtype=xyz.dtype, device=xyz.device) if out is None else \
         _need(out, "out", (n_env, n_max, K), xyz.dtype, xyz.device)
     status, check = _csr_status(status, check, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_radial_expansion(_ptr(xyz), _ptr(offsets), n_env, n, _ptr(R), int(n_max), int(l_max),
-                                          int(bool(normalize)), _dtype_code(xyz), _ptr(c), _ptr(status),
-                                          _stream(xyz.device)))
+    _call(xyz.device, lib().sph_radial_expansion, _ptr(xyz), _ptr(offsets), n_env, n, _ptr(R), int(n_max), int(l_max),
+          int(bool(normalize)), _dtype_code(xyz), _ptr(c), _ptr(status))
     _raise_on_status(status, check)
     return c
 
@@ -460,11 +460,8 @@ def sph_radial_expansion_backward(xyz: torch.Tensor, offsets: torch.Tensor, R: t
     gx = torch.empty((n, 3), dtype=xyz.dtype, device=xyz.device) if want_grad_xyz else None
     gR = torch.empty_like(R) if want_grad_R else None
     status, check = _csr_status(status, check, xyz.device)
-    with torch.cuda.device(xyz.device):
-        _check(lib().sph_radial_expansion_backward(_ptr(xyz), _ptr(offsets), n_env, n, _ptr(R), int(n_max),
-                                                   int(l_max), int(bool(normalize)), _dtype_code(xyz),
-                                                   _ptr(grad_c), _ptr(gx), _ptr(gR), _ptr(status),
-                                                   _stream(xyz.device)))
+    _call(xyz.device, lib().sph_radial_expansion_backward, _ptr(xyz), _ptr(offsets), n_env, n, _ptr(R), int(n_max),
+          int(l_max), int(bool(normalize)), _dtype_code(xyz), _ptr(grad_c), _ptr(gx), _ptr(gR), _ptr(status))
     _raise_on_status(status, check)
     return gx, gR
 
