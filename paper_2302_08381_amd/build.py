@@ -56,6 +56,8 @@ SOURCES = [
     "sph_kernels_expbwd_f32_n1.hip",
     "sph_kernels_expbwd_f64_n0.hip",
     "sph_kernels_expbwd_f64_n1.hip",
+    "sph_kernels_dbwd_f32.hip",
+    "sph_kernels_dbwd_f64.hip",
     "sph_kernels_hess_f32.hip",
     "sph_kernels_hess_f64.hip",
     "sph_kernels_e3nn.hip",

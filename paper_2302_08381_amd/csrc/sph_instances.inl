@@ -2,11 +2,10 @@
 // one kernel family.  Included by the sph_kernels_*.hip translation units with
 // SPH_T, SPH_SUFFIX and SPH_FAMILY defined: 1 = values-only forward and 3 =
 // forward with derivatives (mode SPH_MODE), both for one normalisation
-// SPH_NORM; 2 = backward and double backward.
+// SPH_NORM; 2 = backward.
 #include <utility>
 
 #include "sph_bwd.inl"
-#include "sph_dbwd.inl"
 #include "sph_fwd.inl"
 #include "sph_fwd1.inl"
 #include "sph_fwd4.inl"
@@ -139,33 +138,9 @@ struct Tables {
 };
 
 #else
-// Double backward: one wave per 64-point tile, or (one group of degrees:
-// l_max <= 12 float, <= 8 double) the degree-split block of two waves.
-constexpr int kDbwdSplitMax = std::is_same_v<T, float> ? 12 : 8;
-
-template <bool NORM, int MM, int DS>
-const void* dbwd_ptr() {
-  if constexpr (DS == 2 && MM > kDbwdSplitMax)
-    return nullptr;
-  else
-    return reinterpret_cast<const void*>(&k_dbwd<T, MM, NORM, DS>);
-}
-
-template <bool NORM, int DS, int... Is>
-void fill_dbwd(const void** out, std::integer_sequence<int, Is...>) {
-  const void* tbl[] = {dbwd_ptr<NORM, kBuckets[Is], DS>()...};
-  for (size_t i = 0; i < sizeof...(Is); ++i) out[i] = tbl[i];
-}
-
 struct Tables {
-  const void* dbwd[2][kNumBuckets];
-  const void* dbwd_split[2][kNumBuckets];
   const void* bwd[2];  // one and two waves per block
   Tables() {
-    fill_dbwd<false, 1>(dbwd[0], Buckets{});
-    fill_dbwd<true, 1>(dbwd[1], Buckets{});
-    fill_dbwd<false, 2>(dbwd_split[0], Buckets{});
-    fill_dbwd<true, 2>(dbwd_split[1], Buckets{});
     bwd[0] = reinterpret_cast<const void*>(&k_bwd<T, 1>);
     bwd[1] = reinterpret_cast<const void*>(&k_bwd<T, 2>);
   }
@@ -268,16 +243,6 @@ KernelInfo SPH_CAT(bwd_info_, SPH_SUFFIX)(int L) {
   const bool lds_bound = std::is_same_v<T, float> && 4 * lds > 160 * 1024;
   const int bpc = pipe && !lds_bound ? 1 : 0;
   return KernelInfo{tables().bwd[nw - 1], lds, lds, 16 * nw, kWave * nw, bpc};
-}
-
-KernelInfo SPH_CAT(dbwd_info_, SPH_SUFFIX)(int L, int normalize) {
-  if (!in_range(L) || (normalize != 0 && normalize != 1)) return KernelInfo{nullptr, 0, 0, 0, 0};
-  const size_t lds = sizeof(T) * kWave * static_cast<size_t>(tile_stride<T>(L, kDbwdBudget<T>));
-  const bool one_group = group_end(0, L, kDbwdBudget<T>) > L;
-  const void* split = tables().dbwd_split[normalize][bucket_index(L)];
-  if (one_group && split != nullptr)  // + wave 1's Hessian sums
-    return KernelInfo{split, lds + 3 * kWave * sizeof(T), lds + 3 * kWave * sizeof(T), kWave, 2 * kWave};
-  return KernelInfo{tables().dbwd[normalize][bucket_index(L)], lds, lds, kWave, kWave};
 }
 #endif
 

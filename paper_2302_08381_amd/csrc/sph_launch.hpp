@@ -49,6 +49,7 @@ struct DbwdParams {
   int32_t L;
   void* ggY;   // nullable
   void* gxyz2; // nullable
+  int32_t tile;  // points per block
 };
 
 // Explicit Hessians (k_hess).
