@@ -566,9 +566,9 @@ def _suite_workloads():
         ("hessian: Y+dY", "k_fwd4<float, 6, 6,", n3 * 4 * (3 + 4 * K6),
          "the forward half of sph_compute_with_hessians, same 4e6 points, l_max = 6"),
         ("hessian: d2Y", "k_hess<float", n3 * 4 * (3 + 9 * K6), "d2Y [n,3,3,K], same points"),
-        ("radial expansion", "k_expand<float", npt * 4 * (3 + (L + 1) * NM) + ne * (8 + 4 * NM * K8),
+        ("radial expansion", "k_expfwd<float", npt * 4 * (3 + (L + 1) * NM) + ne * (8 + 4 * NM * K8),
          f"{ne} environments ({npt} points), l_max = 8, 8 channels, float32"),
-        ("radial expansion backward", "k_expand_bwd<float",
+        ("radial expansion backward", "k_expbwd<float",
          npt * 4 * (3 + 2 * (L + 1) * NM + 3) + ne * (8 + 4 * NM * K8), "grad_xyz and grad_R, same environments"),
     ]
 

@@ -23,7 +23,7 @@
 // TB/s of 0.46 GB), l_max 12 325 -> 232; 16 channels l_max 8 439 -> 210; 5
 // channels l_max 8 232 -> 137; double 4 channels l_max 6 180 -> 108, 8
 // channels l_max 8 363 -> 281; 136 000 points in 2000 environments, double 5
-// channels l_max 6 48 -> 26.  What is left is arithmetic and LDS: the
+// channels l_max 6 48 -> 24.  What is left is arithmetic and LDS: the
 // harmonics take about a third of a chunk, the contraction most of the rest.
 #pragma once
 
@@ -117,6 +117,9 @@ __global__ __launch_bounds__(kWave * WV) void k_expfwd(ExpandParams P) {
   using F = ExpFwd<T, LT, CW, NG, WV>;
   using V = typename Vec16<T>::type;
   constexpr int W = Vec16<T>::n;
+  // an item's channels as the widest vectors that divide them
+  constexpr int CV = CW % W == 0 ? W : 2;
+  typedef T C __attribute__((ext_vector_type(CV)));
   constexpr int NT = kWave * WV;
   constexpr int L = LT, K = F::K, NP = F::NP, SY = F::SY, RS = F::RS, CP = F::CP;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -302,14 +305,14 @@ __global__ __launch_bounds__(kWave * WV) void k_expfwd(ExpandParams P) {
 #pragma unroll 2
           for (int j = s + part; j < t; j += F::parts) {
             const T vp = yp[j * SY], vm = ym[j * SY];
-            const V* r = reinterpret_cast<const V*>(rp + j * RS);
+            const C* r = reinterpret_cast<const C*>(rp + j * RS);
 #pragma unroll
-            for (int a = 0; a < CW / W; ++a) {
-              const V q = r[a];
+            for (int a = 0; a < CW / CV; ++a) {
+              const C q = r[a];
 #pragma unroll
-              for (int u = 0; u < W; ++u) {
-                ap[a * W + u] += q[u] * vp;
-                am[a * W + u] += q[u] * vm;
+              for (int u = 0; u < CV; ++u) {
+                ap[a * CV + u] += q[u] * vp;
+                am[a * CV + u] += q[u] * vm;
               }
             }
           }

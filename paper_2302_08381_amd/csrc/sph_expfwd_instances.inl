@@ -12,18 +12,30 @@ namespace {
 
 using T = SPH_T;
 constexpr int kSlots = kCompileMax<T> + 1;
-constexpr int kLayouts = 4;
+constexpr int kLayouts = 6;
 
-// Layouts of the channels, groups of CW:  Three groups of four for 9..12
-// channels where a part fits the block (float, l_max 6, 12 channels: 125 us
-// against 190 as two groups of eight; l_max 8 195 and 244).
-constexpr int layout_cw(int i) { return i == 0 || i == 2 ? 4 : 8; }
-constexpr int layout_ng(int i) { return i == 2 ? 3 : (i == 3 ? 2 : 1); }
+// Layouts of the channels, groups of CW: 4, 8, three of 4, two of 8, and in
+// double 6 and two of 6.  Three groups of four for 9..12 channels where a part
+// fits the block (float, 12 channels, 20 000 environments: l_max 6 125 us
+// against 190 as two groups of eight; l_max 8 195 and 244).  In double the LDS
+// tile of the padded channels costs blocks: six for 5 and 6 channels up to
+// l_max 7 (5 channels, 10 000 environments, against eight: l_max 4 51 and 66
+// us, l_max 5 65 and 86, l_max 6 85 and 92, l_max 7 92 and 133; but l_max 8
+// 171 and 147; float l_max 8, 20 000, 128 and 131), two of six for 9..12 at
+// l_max 8 (9 channels 181 against 213 as three of four; l_max 6 149 and 134).
+constexpr int layout_cw(int i) { return i == 0 || i == 2 ? 4 : (i >= 4 ? 6 : 8); }
+constexpr int layout_ng(int i) { return i == 2 ? 3 : (i == 3 || i == 5 ? 2 : 1); }
 constexpr bool layout_serves(int L, int i) {
+  if (i == 4) return sizeof(T) == 8 && L <= 7;
+  if (i == 5) return sizeof(T) == 8 && L >= 8;
   return (L + 1) * (L + 2) / 2 * layout_ng(i) <= kWave * 4;
 }
 constexpr int layout_of(int L, int n_max) {
-  return n_max <= 4 ? 0 : (n_max <= 8 ? 1 : (n_max <= 12 && layout_serves(L, 2) ? 2 : 3));
+  if (n_max <= 4) return 0;
+  if (n_max <= 6 && layout_serves(L, 4)) return 4;
+  if (n_max <= 8) return 1;
+  if (n_max > 12) return 3;
+  return layout_serves(L, 5) ? 5 : (layout_serves(L, 2) ? 2 : 3);
 }
 
 template <int LT, int I, int WV, bool VEC>
@@ -58,6 +70,8 @@ struct Tables {
     fill<1>();
     fill<2>();
     fill<3>();
+    fill<4>();
+    fill<5>();
   }
 };
 

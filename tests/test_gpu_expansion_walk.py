@@ -29,7 +29,7 @@ COUNTS = {
 # which three groups of four need more than the block's threads, and of the
 # largest degrees and channels that the compile-time kernel takes
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64])
-@pytest.mark.parametrize("l_max,n_max", [(0, 1), (0, 16), (1, 4), (3, 9), (5, 8), (6, 5), (8, 12), (8, 16), (9, 3), (11, 12),
+@pytest.mark.parametrize("l_max,n_max", [(0, 1), (0, 16), (1, 4), (3, 9), (5, 8), (6, 5), (4, 6), (7, 6), (8, 6), (8, 9), (8, 12), (8, 16), (9, 3), (11, 12),
                                          (12, 12), (12, 16), (13, 8), (4, 17)])
 @pytest.mark.parametrize("counts", sorted(COUNTS))
 def test_forward_walk(counts, l_max, n_max, dt):
