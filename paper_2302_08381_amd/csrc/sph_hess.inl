@@ -24,12 +24,14 @@
 // in float), so the orders and signs are what fills its waves; a lane per row
 // of the 3x3 block forms each off-diagonal entry twice and the shared factors
 // three times (VALU 85 % busy).  Measured against that, 1e6 points: float
-// l_max 3 124 -> 100 us, l_max 6 392 -> 308 (5.7 TB/s of stores), l_max 8
-// (500 000) 511 -> 260, l_max 12 (300 000) 1242 -> 359; double l_max 4 (500
-// 000) 192 -> 158, l_max 8 (300 000) 827 -> 312; l_max 32 float (30 000) 1395
-// -> 415, double (10 000) 1156 -> 326.  What is left is the stores up to l_max
-// 8; past it the few waves that the tile leaves.  Error against double, float
-// l_max 6 / 12: 5e-7 / 6e-7 of a point's largest entry (1.6e-6 / 2e-6).
+// l_max 3 124 -> 106 us, l_max 6 392 -> 300 (5.9 TB/s of stores), l_max 8
+// (500 000) 511 -> 250, l_max 12 (300 000) 1242 -> 340; double l_max 4 (500
+// 000) 192 -> 158, l_max 8 (300 000) 827 -> 300; l_max 32 float (30 000) 1395
+// -> 398, double (10 000) 1156 -> 316.  What is left up to l_max 12 is close
+// to the stores, with the VALU as busy: about 98 operations per column, of
+// which the lanes below their order waste a quarter; past it the few waves
+// that the tile leaves.  Error against double, float l_max 6 / 12: 5e-7 / 6e-7
+// of a point's largest entry (1.6e-6 / 2e-6).
 #pragma once
 
 #include "sph_ord.inl"
@@ -37,11 +39,14 @@
 namespace sph {
 
 // LDS elements of a tile of `points` Hessians.  A point's nine rows take a
-// stride that is padded by one 16-byte vector where it would be a multiple of
-// 16 banks (odd l_max), so that the lanes of one order hit distinct ones.
+// stride that is padded by one 16-byte vector where it would bring the lanes of
+// one order to few banks: float l_max + 1 a multiple of 4 (9 K is then a
+// multiple of 16; else it is odd, or 4 times an odd number, which keeps 16
+// points and 4 orders apart), double odd l_max.
 template <typename T>
 __host__ __device__ constexpr int hess_pad(int L) {
-  return (L & 1) != 0 ? 16 / static_cast<int>(sizeof(T)) : 0;
+  if (sizeof(T) == 4) return (L + 1) % 4 == 0 ? 4 : 0;
+  return (L & 1) != 0 ? 2 : 0;
 }
 template <typename T>
 __host__ __device__ constexpr size_t hess_lds_bytes(int L, int points) {
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
   const int L = LT >= 0 ? LT : P.L;
   const int K = (L + 1) * (L + 1), R9 = 9 * K;
   const int pad = hess_pad<T>(L), S9 = R9 + pad;
-  const int PT = P.tile;
+  const int PT = LT >= 0 ? hess_points<T>(LT) : P.tile;
   const int tid = threadIdx.x, nt = blockDim.x;
   const OrdTable<T>& C = ord_table<T>(0);
   const int half = SP == 2 ? nt / 2 : nt;  // whole waves
@@ -155,7 +160,9 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
         tpB = tmB;
       }
     }
+    const T tp2x = tpx + tpx, tp2y = tpy + tpy, tm2x = tmx + tmx, tm2y = tmy + tmy;
     const T x = static_cast<T>(ux), y = static_cast<T>(uy), z = static_cast<T>(uz);
+    const T x2 = x + x, y2 = y + y, z2 = z + z;
     const T ir2 = static_cast<T>(ui * ui);
     const T rho2 = static_cast<T>(ux * ux + uy * uy);
     // fx = l - m; p1, p2, e1, w1: the degrees below; d, f, g: see OrdChain
@@ -173,27 +180,27 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
         const T xW = x * Wn;
         const T Qxx = x * xW + Tm, Qxy = y * xW, Qyy = y * (y * Wn) + Tm;
         const T Qxz = x * V, Qyz = y * V;
-        const T lx = fl * x, ly = fl * y, lz = fl * z;
         const T hl = (T(0.5) * fl + T(1)) * q;  // (l + 2)/2 q
-        auto col = [&](T* o, T t, T tx, T ty, T A, T B) {
-          T hxx = Qxx * t + (T(2) * Qx * tx + q * A);
-          T hyy = Qyy * t + (T(2) * Qy * ty - q * A);
+        auto col = [&](T* o, T t, T tx, T ty, T tx2, T ty2, T A, T B) {
+          T hxx = Qxx * t + (Qx * tx2 + q * A);
+          T hyy = Qyy * t + (Qy * ty2 - q * A);
           T hxy = Qxy * t + (Qx * ty + (Qy * tx + q * B));
           T hxz = Qxz * t + Z * tx;
           T hyz = Qyz * t + Z * ty;
           T hzz = U * t;
           if constexpr (NORM) {
-            const T h = hl * t;
-            const T sx = Qx * t + (q * tx - h * x);
-            const T sy = Qy * t + (q * ty - h * y);
-            const T sz = Z * t - h * z;
-            const T ly0 = fl * (q * t);
-            hxx -= T(2) * (lx * sx) + ly0;
-            hyy -= T(2) * (ly * sy) + ly0;
-            hzz -= T(2) * (lz * sz) + ly0;
-            hxy -= lx * sy + ly * sx;
-            hxz -= lx * sz + lz * sx;
-            hyz -= ly * sz + lz * sy;
+            // ls = l s, so that u enters as it is
+            const T lt = fl * t, h = hl * lt;
+            const T sx = Qx * lt + (q * (fl * tx) - h * x);
+            const T sy = Qy * lt + (q * (fl * ty) - h * y);
+            const T sz = Z * lt - h * z;
+            const T ly = q * lt;
+            hxx -= x2 * sx + ly;
+            hyy -= y2 * sy + ly;
+            hzz -= z2 * sz + ly;
+            hxy -= x * sy + y * sx;
+            hxz -= x * sz + z * sx;
+            hyz -= y * sz + z * sy;
           }
           o[0] = hxx;
           o[K] = hxy;
@@ -205,8 +212,8 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
           o[7 * K] = hyz;
           o[8 * K] = hzz;
         };
-        col(base, tp, tpx, tpy, tpA, tpB);
-        if constexpr (SP == 1) col(basm, tm, tmx, tmy, tmA, tmB);
+        col(base, tp, tpx, tpy, tp2x, tp2y, tpA, tpB);
+        if constexpr (SP == 1) col(basm, tm, tmx, tmy, tm2x, tm2y, tmA, tmB);
         // one degree up
         const T a = fx * inv;
         g = a * (z * g - (rho2 * w1 + T(4) * e1));
