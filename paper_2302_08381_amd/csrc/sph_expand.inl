@@ -3,8 +3,8 @@
 //                      R[j, l, n] * Y_l^m(x_j)
 // with the radial values R[j, l, n] supplied by the caller, and its
 // backward, for the degrees and channels that the compile-time kernels
-// (k_expfwd, k_expbwd) leave: degrees past kCompileMax, and in the forward
-// more than 16 channels.  The harmonics never leave the chip.  Forward: a
+// (k_expfwd, k_expbwd) leave: degrees past 12 (in the double backward 8), and in
+// the forward more than 16 channels.  The harmonics never leave the chip.  Forward: a
 // block takes one
 // environment at a time, writes the values of a chunk of its points into an
 // LDS tile, copies the chunk's radial values next to it, and contracts the

@@ -1,5 +1,4 @@
-// Radial expansion for compile-time degrees (float l_max <= 12, double <= 8)
-// and up to 16 channels:
+// Radial expansion for compile-time degrees (l_max <= 12) and up to 16 channels:
 //   c[e, n, l^2+l+m] = sum over the points j of environment e of
 //                      R[j, l, n] * Y_l^m(x_j)
 // (sph_expand.inl holds the kernel for the rest).

@@ -11,7 +11,7 @@ namespace sph {
 namespace {
 
 using T = SPH_T;
-constexpr int kSlots = kCompileMax<T> + 1;
+constexpr int kSlots = kExpFwdMaxL + 1;
 constexpr int kLayouts = 6;
 
 // Layouts of the channels, groups of CW: 4, 8, three of 4, two of 8, and in
@@ -27,7 +27,7 @@ constexpr int layout_cw(int i) { return i == 0 || i == 2 ? 4 : (i >= 4 ? 6 : 8);
 constexpr int layout_ng(int i) { return i == 2 ? 3 : (i == 3 || i == 5 ? 2 : 1); }
 constexpr bool layout_serves(int L, int i) {
   if (i == 4) return sizeof(T) == 8 && L <= 7;
-  if (i == 5) return sizeof(T) == 8 && L >= 8;
+  if (i == 5) return sizeof(T) == 8 && L >= 8 && (L + 1) * (L + 2) <= kWave * 4;
   return (L + 1) * (L + 2) / 2 * layout_ng(i) <= kWave * 4;
 }
 constexpr int layout_of(int L, int n_max) {

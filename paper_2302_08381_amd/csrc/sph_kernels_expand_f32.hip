@@ -79,7 +79,7 @@ const Tables& tables() {
 
 KernelInfo expand_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n_env) {
   if (L < 0 || L > kMaxLmax || (normalize != 0 && normalize != 1) || n_max < 1) return KernelInfo{nullptr, 0, 0, 0, 0};
-  if (expfwd_serves<T>(L, n_max))
+  if (expfwd_serves(L, n_max))
     return normalize ? expfwd_info_f32_n1(L, n_max, aligned, n_env) : expfwd_info_f32_n0(L, n_max, aligned, n_env);
   const Tables& t = tables();
   const int a = expand_acc(L, n_max) == 8 ? 1 : 0;

@@ -100,14 +100,14 @@ __host__ __device__ constexpr size_t expand_lds_bytes(int L, int n_max, int chun
   return ytile + sizeof(T) * (static_cast<size_t>(chunk) * (L + 1) * np + static_cast<size_t>(np) * K);
 }
 
-// Where the compile-time kernel (k_expfwd) serves: up to kCompileMax and 16
+// Where the compile-time kernel (k_expfwd) serves: up to l_max 12 and 16
 // channels (24 channels, float l_max 8, 5000 environments: 131 us in k_expand
-// against 145 as two groups of 16).
+// against 145 as two groups of 16).  Double past l_max 8, 3000 environments,
+// against run-time degrees: l_max 9 3 channels 80 -> 36 us, 12 194 -> 78;
+// l_max 10 8 channels 134 -> 65, 16 193 -> 157.
+constexpr int kExpFwdMaxL = 12;
 constexpr int kExpFwdChannels = 16;
-template <typename T>
-constexpr bool expfwd_serves(int L, int n_max) {
-  return L <= kCompileMax<T> && n_max <= kExpFwdChannels;
-}
+constexpr bool expfwd_serves(int L, int n_max) { return L <= kExpFwdMaxL && n_max <= kExpFwdChannels; }
 // Its waves.  Up to l_max 4 two, whose blocks are more numerous (8 channels,
 // 20 000 environments of 68 points, two / four waves: float l_max 4 55 / 65
 // us, l_max 6 91 / 87, double l_max 4 112 / 161), unless the environments
