@@ -2,11 +2,11 @@
 //   c[e, n, l^2+l+m] = sum over the points j of environment e of
 //                      R[j, l, n] * Y_l^m(x_j)
 // with the radial values R[j, l, n] supplied by the caller, and its
-// backward, for the degrees and channels that the compile-time kernels
-// (k_expfwd, k_expbwd) leave: degrees past 12 (in the double backward 8), and in
-// the forward more than 16 channels.  The harmonics never leave the chip.  Forward: a
-// block takes one
-// environment at a time, writes the values of a chunk of its points into an
+// backward, for what the compile-time kernels (k_expfwd, k_expbwd) leave:
+// degrees past 12, more than 16 channels (the forward only) and in the double
+// backward 9..16 channels past l_max 6.  The harmonics never leave the chip.
+// Forward: a block takes one environment at a time, writes the values of a
+// chunk of its points into an
 // LDS tile, copies the chunk's radial values next to it, and contracts the
 // two tiles into per-thread accumulators; partial sums of environments
 // longer than one chunk wait in LDS.  Backward: one lane per point, see

@@ -1,5 +1,5 @@
-// Backward of the radial expansion for compile-time degrees (float
-// l_max <= 12, double <= 8); sph_expand.inl holds the run-time-degree kernel
+// Backward of the radial expansion for compile-time degrees (l_max <= 12, but
+// double with 9..16 channels <= 6); sph_expand.inl holds the run-time-degree kernel
 // and states the sums:
 //   grad_R[j, l, n] = sum_m G[e, n, l^2+l+m] Y_l^m(x_j)
 //   grad_xyz[j, a]  = sum_k gY[j, k] dY_k/dx_a(x_j),

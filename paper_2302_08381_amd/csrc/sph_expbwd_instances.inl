@@ -11,7 +11,7 @@ namespace sph {
 namespace {
 
 using T = SPH_T;
-constexpr int kSlots = kCompileMax<T> + 1;
+constexpr int kSlots = kExpandMaxL + 1;
 
 template <int LT, int NPC, bool VEC>
 const void* fn_ptr() {
@@ -43,7 +43,7 @@ struct Tables {
 
 const void* SPH_CAT(SPH_CAT(SPH_CAT(expbwd_fn_, SPH_SUFFIX), _n), SPH_NORM)(int L, int npc, bool vec) {
   static const Tables t;
-  return L < 0 || L > kCompileMax<T> ? nullptr : t.fn[npc == 16 ? 1 : 0][vec ? 1 : 0][L];
+  return L < 0 || L > kExpandMaxL ? nullptr : t.fn[npc == 16 ? 1 : 0][vec ? 1 : 0][L];
 }
 
 }  // namespace sph

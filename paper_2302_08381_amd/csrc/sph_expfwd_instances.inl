@@ -11,7 +11,7 @@ namespace sph {
 namespace {
 
 using T = SPH_T;
-constexpr int kSlots = kExpFwdMaxL + 1;
+constexpr int kSlots = kExpandMaxL + 1;
 constexpr int kLayouts = 6;
 
 // Layouts of the channels, groups of CW: 4, 8, three of 4, two of 8, and in

@@ -37,7 +37,7 @@ void fill_spec(const void** out, std::integer_sequence<int, Ls...>) {
 // compile-time one.
 template <bool NORM, int NPC, int MM>
 const void* bwd_ptr() {
-  if constexpr (MM > kCompileMax<T> || !expbwd_serves<T>(MM, NPC))
+  if constexpr (!expbwd_serves<T>(MM, NPC))
     return reinterpret_cast<const void*>(&k_expand_bwd<T, MM, NORM, NPC>);
   else
     return nullptr;

@@ -105,9 +105,9 @@ __host__ __device__ constexpr size_t expand_lds_bytes(int L, int n_max, int chun
 // against 145 as two groups of 16).  Double past l_max 8, 3000 environments,
 // against run-time degrees: l_max 9 3 channels 80 -> 36 us, 12 194 -> 78;
 // l_max 10 8 channels 134 -> 65, 16 193 -> 157.
-constexpr int kExpFwdMaxL = 12;
+constexpr int kExpandMaxL = 12;
 constexpr int kExpFwdChannels = 16;
-constexpr bool expfwd_serves(int L, int n_max) { return L <= kExpFwdMaxL && n_max <= kExpFwdChannels; }
+constexpr bool expfwd_serves(int L, int n_max) { return L <= kExpandMaxL && n_max <= kExpFwdChannels; }
 // Its waves.  Up to l_max 4 two, whose blocks are more numerous (8 channels,
 // 20 000 environments of 68 points, two / four waves: float l_max 4 55 / 65
 // us, l_max 6 91 / 87, double l_max 4 112 / 161), unless the environments
@@ -155,11 +155,12 @@ constexpr int kExpBwdSlices = 4;
 // against order-m tables formed twice.  Float, 20 000 environments, 1 / 2 / 4
 // waves: 8 channels l_max 3 72 / 73 us, l_max 4 88.7 / 88.6, l_max 8 - / 210 /
 // 240, l_max 12 - / 455 / 339; 16 channels (10 000) l_max 12 - / 832 / 508.
-// Double, 8 channels l_max 3 180 / 201, l_max 8 - / 490 / 612.
+// Double, 8 channels l_max 3 180 / 201, l_max 8 - / 490 / 612; 3000 environments
+// l_max 10 - / 116 / 160.
 template <typename T>
 constexpr int expbwd_waves(int L, int npc) {
   if (L <= (npc == 8 ? (sizeof(T) == 4 ? 4 : 5) : 3)) return 1;
-  return sizeof(T) == 4 && L >= (npc == 8 ? 12 : 11) ? 4 : 2;
+  return L >= (npc == 8 && sizeof(T) == 4 ? 12 : 11) ? 4 : 2;
 }
 // Environments per chunk: four with 8 channels (l_max 8 float 210 us against
 // 221 with two, double 490 and 533; all eight that a wider walk would allow
@@ -173,13 +174,14 @@ constexpr int expbwd_slices(int npc, int64_t n, int64_t n_env) {
   if (npc == 8) return kExpBwdSlices;
   return n / (n_env > 0 ? n_env : 1) >= 12 ? 2 : (sizeof(T) == 4 ? 4 : 3);
 }
-// Where the compile-time kernel is the faster one: up to kCompileMax, but not
-// double with 16 channels past l_max 6, whose registers spill (10 000
+// Where the compile-time kernel is the faster one: up to l_max 12, but not
+// double with 9..16 channels past l_max 6, whose registers spill (10 000
 // environments, l_max 8: 716 us against the run-time-degree kernel's 539;
-// l_max 6 356 against 400).
+// l_max 6 356 against 400).  Double past l_max 8, 3000 environments, 8
+// channels: l_max 9 99 us against 164, l_max 12 156 against 255.
 template <typename T>
 constexpr bool expbwd_serves(int L, int npc) {
-  return L <= kCompileMax<T> && !(sizeof(T) == 8 && npc == 16 && L >= 7);
+  return L <= kExpandMaxL && !(sizeof(T) == 8 && npc == 16 && L >= 7);
 }
 template <typename T>
 constexpr size_t expbwd_lds_bytes(int L, int np, int slices, int waves) {

@@ -47,7 +47,7 @@ def test_forward_walk(counts, l_max, n_max, dt):
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64])
-@pytest.mark.parametrize("l_max,n_max", [(0, 8), (3, 8), (4, 5), (5, 16), (8, 8), (7, 16), (12, 8), (9, 12)])
+@pytest.mark.parametrize("l_max,n_max", [(0, 8), (3, 8), (4, 5), (5, 16), (8, 8), (7, 16), (10, 5), (11, 8), (12, 8), (9, 12)])
 @pytest.mark.parametrize("counts", sorted(COUNTS))
 def test_backward_walk(counts, l_max, n_max, dt):
     import paper_2302_08381_amd as sph
