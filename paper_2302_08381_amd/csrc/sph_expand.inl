@@ -92,14 +92,23 @@ __device__ __forceinline__ void env_range(const int64_t* o, int64_t e, int64_t n
   t = hi;
 }
 
-// First e in [0, n_env] with o[e] >= p, found by the W lanes base .. base+W-1
-// of the wave together: each round probes W evenly spaced offsets at once and
-// keeps the gap where the comparison turns, so log_W(n_env) rounds of one
-// dependent load replace log_2(n_env).  Every lane of the wave must call it
-// (it votes across the wave); each group gets its own answer.  With offsets
-// that are not sorted the result is still in [0, n_env].
-__device__ __forceinline__ int64_t group_lower_bound(const int64_t* o, int64_t n_env, int64_t p, int gl, int base,
-                                                     int W) {
+// The first environment of share g of G: the first e in [0, n_env] with
+// o[e] + e >= g (n + n_env) / G.  A share is an even part of the points and
+// the environments together, so a run of empty environments (whose zeros the
+// forward writes) spreads over the blocks as points do; every environment is
+// in exactly one share.  By points alone a run of empty ones fell to the block
+// of the point it stands at: float, 100 000 empty environments, l_max 3, 8
+// channels 9368 us against 15; half of 100 000 empty, the others of 8 points,
+// 4720 against 50, backward 7258 against 42.
+// Found by the W lanes base .. base+W-1 of the wave together: each round
+// probes W evenly spaced offsets at once and keeps the gap where the
+// comparison turns, so log_W(n_env) rounds of one dependent load replace
+// log_2(n_env).  Every lane of the wave must call it (it votes across the
+// wave); each group gets its own answer.  With offsets that are not sorted the
+// result is still in [0, n_env].
+__device__ __forceinline__ int64_t group_share(const int64_t* o, int64_t n_env, int64_t n, int64_t g, int64_t G,
+                                               int gl, int base, int W) {
+  const int64_t p = g * (n + n_env) / G;
   int rounds = 1;  // the same for every lane: W^rounds > n_env
   for (int64_t span = W; span <= n_env; span *= W) ++rounds;
   const unsigned long long gmask = W == 64 ? ~0ull : ((1ull << W) - 1) << base;
@@ -107,7 +116,7 @@ __device__ __forceinline__ int64_t group_lower_bound(const int64_t* o, int64_t n
   for (int r = 0; r < rounds; ++r) {
     const int64_t step = (hi - lo + W - 1) / W;
     const int64_t q = lo + gl * step;
-    const bool less = step > 0 && q < hi && o[q] < p;
+    const bool less = step > 0 && q < hi && o[q] < p - q;
     const int c = __popcll(__ballot(less) & gmask);
     if (step > 0) {  // the answer is in (q_{c-1}, q_c]
       const int64_t qc = lo + c * step;
@@ -168,10 +177,8 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandParams P) {
     if (tid == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // The blocks split the points evenly: block g of G takes the environments
-  // that start in points [g n / G, (g+1) n / G) (found by searching the
-  // offsets; every environment has one start, so each goes to exactly one
-  // block; see kEven for small l_max).  The block walks its chunks (up to
+  // Block g of G takes share g of the environments (group_share; see kEven for
+  // small l_max).  The block walks its chunks (up to
   // JC consecutive points, within one environment or across the end of one
   // into the next, see shape) as a pipeline: the coordinates and the first
   // radial batch
@@ -191,7 +198,7 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandParams P) {
   if constexpr (kEven) {
     // each wave finds both ends at once: lanes 0..31 the start, 32..63 the end
     const int wl = tid % kWave, half = wl / 32;
-    const int64_t bound = group_lower_bound(P.offsets, P.n_env, (g + half) * P.n / G, wl % 32, half * 32, 32);
+    const int64_t bound = group_share(P.offsets, P.n_env, P.n, g + half, G, wl % 32, half * 32, 32);
     e = __shfl(bound, 0);
     e_end = g + 1 == G ? P.n_env : __shfl(bound, 32);
   }
@@ -771,14 +778,11 @@ __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
     if (lane == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // The blocks split the points evenly: block g of G takes the environments
-  // that start in points [g n / G, (g+1) n / G) (found by searching the
-  // offsets; every environment has one start, so each goes to exactly one
-  // block).  State: environment e, its range [b, t), the chunk start j0
+  // Block g of G takes share g of the environments (group_share).  State: environment e, its range [b, t), the chunk start j0
   // (b <= j0 < t), and which environment each G slice holds.
   const int64_t G = gridDim.x, g = blockIdx.x;
-  int64_t e = group_lower_bound(P.offsets, P.n_env, g * P.n / G, gl, 0, GS);
-  const int64_t e_last = group_lower_bound(P.offsets, P.n_env, (g + 1) * P.n / G, gl, 0, GS);
+  int64_t e = group_share(P.offsets, P.n_env, P.n, g, G, gl, 0, GS);
+  const int64_t e_last = group_share(P.offsets, P.n_env, P.n, g + 1, G, gl, 0, GS);
   const int64_t e_end = g + 1 == G ? P.n_env : e_last;
   int64_t b = 0, t = 0, j0 = 0;
   // first non-empty environment at or after ee (e_end if none), its range

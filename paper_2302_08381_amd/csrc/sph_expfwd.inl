@@ -138,14 +138,13 @@ __global__ __launch_bounds__(kWave * WV) void k_expfwd(ExpandParams P) {
     if (lane == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // Block g of G takes the environments that start in points
-  // [g n / G, (g+1) n / G) (each has one start, so goes to one block); each
-  // wave finds both ends at once, lanes 0..31 the first, 32..63 the last.
+  // Block g of G takes share g of the environments (group_share); each wave
+  // finds both ends at once, lanes 0..31 the first, 32..63 the last.
   const int64_t G = gridDim.x, g = blockIdx.x;
   int64_t e, e_end;
   {
     const int half = lane / 32;
-    const int64_t bound = group_lower_bound(P.offsets, P.n_env, (g + half) * P.n / G, lane % 32, half * 32, 32);
+    const int64_t bound = group_share(P.offsets, P.n_env, P.n, g + half, G, lane % 32, half * 32, 32);
     e = uniform64(__shfl(bound, 0));
     e_end = g + 1 == G ? P.n_env : uniform64(__shfl(bound, 32));
   }
