@@ -497,7 +497,7 @@ int32_t sph_compute_with_hessians(const void* xyz, int64_t n, int32_t l_max, int
   sph::FwdParams pf{xyz, n, l_max, Y, dY, nullptr, nullptr, nullptr, 0, nullptr, kf.tile_points};
   e = launch(kf.fn, static_cast<unsigned>(plain_grid(ceil_div(n, kf.tile_points))), kf.block, kf.lds_bytes, &pf, s);
   if (e != hipSuccess) return device_fail(e, "forward launch");
-  sph::HessParams ph{xyz, n, l_max, d2Y, kh.tile_points};
+  sph::HessParams ph{xyz, n, l_max, d2Y, kh.tile_points, sph::scaled_reach2(l_max, dtype == SPH_F64)};
   e = launch(kh.fn, static_cast<unsigned>(plain_grid(ceil_div(n, kh.tile_points))), kh.block, kh.lds_bytes, &ph, s);
   if (e != hipSuccess) return device_fail(e, "hessian launch");
   return ok();

@@ -165,68 +165,59 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
     const T x2 = x + x, y2 = y + y, z2 = z + z;
     const T ir2 = static_cast<T>(ui * ui);
     const T rho2 = static_cast<T>(ux * ux + uy * uy);
-    // fx = l - m; p1, p2, e1, w1: the degrees below; d, f, g: see OrdChain
-    T fx = T(0), pv = T(1), p1 = T(0), p2 = T(0), d = T(0), e = T(0), e1 = T(0), f = T(0), w = T(0), w1 = T(0), g = T(0);
+    HessChain<T> ch{z, rho2};
     T* base = st + sh + p * S9 + l0 * l0 + l0 + (SP == 2 && part == 1 ? -mm : mm);
     T* basm = base - 2 * mm;
     T fl = T(l0);
+    // the columns of degree l (fl) at o and, with one wave per order, om
+    auto entries = [&](T N, T* o, T* om, auto mul) {
+      if constexpr (NORM) N *= ir2;
+      const T q = N * ch.p, Tm = N * ch.e, Wn = N * ch.w;
+      const T Nx = N * ch.x;
+      const T Z = Nx * ch.p1, V = Nx * ch.e1, U = Nx * ((ch.x - T(1)) * ch.p2);
+      const T Qx = mul(x, Tm), Qy = mul(y, Tm);
+      const T xW = mul(x, Wn);
+      const T Qxx = mul(x, xW) + Tm, Qxy = mul(y, xW), Qyy = mul(y, mul(y, Wn)) + Tm;
+      const T Qxz = mul(x, V), Qyz = mul(y, V);
+      const T hl = (T(0.5) * fl + T(1)) * q;  // (l + 2)/2 q
+      auto col = [&](T* c, T t, T tx, T ty, T tx2, T ty2, T A, T B) {
+        T hxx = mul(Qxx, t) + (mul(Qx, tx2) + mul(q, A));
+        T hyy = mul(Qyy, t) + (mul(Qy, ty2) - mul(q, A));
+        T hxy = mul(Qxy, t) + (mul(Qx, ty) + (mul(Qy, tx) + mul(q, B)));
+        T hxz = mul(Qxz, t) + mul(Z, tx);
+        T hyz = mul(Qyz, t) + mul(Z, ty);
+        T hzz = mul(U, t);
+        if constexpr (NORM) {
+          // ls = l s, so that u enters as it is
+          const T lt = fl * t, h = hl * lt;
+          const T sx = Qx * lt + (q * (fl * tx) - h * x);
+          const T sy = Qy * lt + (q * (fl * ty) - h * y);
+          const T sz = Z * lt - h * z;
+          const T ly = q * lt;
+          hxx -= x2 * sx + ly;
+          hyy -= y2 * sy + ly;
+          hzz -= z2 * sz + ly;
+          hxy -= x * sy + y * sx;
+          hxz -= x * sz + z * sx;
+          hyz -= y * sz + z * sy;
+        }
+        c[0] = hxx;
+        c[K] = hxy;
+        c[2 * K] = hxz;
+        c[3 * K] = hxy;
+        c[4 * K] = hyy;
+        c[5 * K] = hyz;
+        c[6 * K] = hxz;
+        c[7 * K] = hyz;
+        c[8 * K] = hzz;
+      };
+      col(o, tp, tpx, tpy, tp2x, tp2y, tpA, tpB);
+      if constexpr (SP == 1) col(om, tm, tmx, tmy, tm2x, tm2y, tmA, tmB);
+    };
     auto degree = [&](int l, T N, T inv) {
       if (lane_on && l >= mm) {
-        if constexpr (NORM) N *= ir2;
-        const T q = N * pv, Tm = N * e, Wn = N * w;
-        const T Nx = N * fx;
-        const T Z = Nx * p1, V = Nx * e1, U = Nx * ((fx - T(1)) * p2);
-        const T Qx = x * Tm, Qy = y * Tm;
-        const T xW = x * Wn;
-        const T Qxx = x * xW + Tm, Qxy = y * xW, Qyy = y * (y * Wn) + Tm;
-        const T Qxz = x * V, Qyz = y * V;
-        const T hl = (T(0.5) * fl + T(1)) * q;  // (l + 2)/2 q
-        auto col = [&](T* o, T t, T tx, T ty, T tx2, T ty2, T A, T B) {
-          T hxx = Qxx * t + (Qx * tx2 + q * A);
-          T hyy = Qyy * t + (Qy * ty2 - q * A);
-          T hxy = Qxy * t + (Qx * ty + (Qy * tx + q * B));
-          T hxz = Qxz * t + Z * tx;
-          T hyz = Qyz * t + Z * ty;
-          T hzz = U * t;
-          if constexpr (NORM) {
-            // ls = l s, so that u enters as it is
-            const T lt = fl * t, h = hl * lt;
-            const T sx = Qx * lt + (q * (fl * tx) - h * x);
-            const T sy = Qy * lt + (q * (fl * ty) - h * y);
-            const T sz = Z * lt - h * z;
-            const T ly = q * lt;
-            hxx -= x2 * sx + ly;
-            hyy -= y2 * sy + ly;
-            hzz -= z2 * sz + ly;
-            hxy -= x * sy + y * sx;
-            hxz -= x * sz + z * sx;
-            hyz -= y * sz + z * sy;
-          }
-          o[0] = hxx;
-          o[K] = hxy;
-          o[2 * K] = hxz;
-          o[3 * K] = hxy;
-          o[4 * K] = hyy;
-          o[5 * K] = hyz;
-          o[6 * K] = hxz;
-          o[7 * K] = hyz;
-          o[8 * K] = hzz;
-        };
-        col(base, tp, tpx, tpy, tp2x, tp2y, tpA, tpB);
-        if constexpr (SP == 1) col(basm, tm, tmx, tmy, tm2x, tm2y, tmA, tmB);
-        // one degree up
-        const T a = fx * inv;
-        g = a * (z * g - (rho2 * w1 + T(4) * e1));
-        w1 = w;
-        w = z * w + g;
-        f = a * (z * f - (rho2 * e1 + T(2) * p1));
-        e1 = e;
-        e = z * e + f;
-        d = a * (z * d - rho2 * p1);
-        p2 = p1;
-        p1 = pv;
-        pv = z * pv + d;
-        fx += T(1);
+        entries(N, base, basm, MulPlain{});
+        ch.advance(inv, MulPlain{});
       }
       fl += T(1);
       base += 2 * l + 2;
@@ -249,10 +240,23 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
       for (int u = 0; u < kOrdStep; ++u) {
         if (l + u <= L) degree(l + u, Ac[2 * u], u + 1 < kOrdStep ? Ac[(2 * u + 3) % (2 * kOrdStep)] : Bc[1]);
         // one degree after the other: interleaved they take more registers
-        asm volatile("" : "+v"(pv), "+v"(p1), "+v"(e), "+v"(w));
+        asm volatile("" : "+v"(ch.p), "+v"(ch.p1), "+v"(ch.e), "+v"(ch.w));
       }
 #pragma unroll
       for (int u = 0; u < 2 * kOrdStep; ++u) Ac[u] = Bc[u];
+    }
+    if constexpr (!NORM) {  // past reach2: once more, see HessChain
+      if (lane_on && !(pt.rxy2 + pt.ez * pt.ez <= static_cast<T>(P.reach2))) {
+        ch = HessChain<T>{z, rho2};
+        T* o = st + sh + p * S9 + (SP == 2 && part == 1 ? -mm : mm);
+        fl = T(mm);
+#pragma unroll 1
+        for (int l = mm; l <= L; ++l) {
+          entries(C.a[l][2 * mm], o + l * l + l, o + l * l + l - 2 * mm, MulZero{});
+          ch.advance(C.a[l + 1][2 * mm + 1], MulZero{});
+          fl += T(1);
+        }
+      }
     }
     __syncthreads();
     const int cnt = np * R9;

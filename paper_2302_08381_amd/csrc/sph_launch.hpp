@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 
 namespace sph {
@@ -59,7 +60,16 @@ struct HessParams {
   int32_t L;
   void* d2Y;        // [n,3,3,K]
   int32_t tile;     // points per block
+  double reach2;    // see scaled_reach2
 };
+
+// Squared distance from the origin up to which the scaled harmonics of
+// l_max, their derivatives and every product on the way to them are within
+// the type's range (r^l times the largest of their factors, below 1e10 for
+// every l <= 32).
+inline double scaled_reach2(int L, bool f64) {
+  return std::pow(f64 ? 1e298 : 1e28, 2.0 / (L > 2 ? L : 2));
+}
 
 // Radial expansion over CSR environments (k_expand).
 struct ExpandParams {

@@ -164,6 +164,52 @@ struct OrdChain {
   }
 };
 
+// The products of the second derivatives: as they are, and with 0 times
+// anything 0.
+struct MulPlain {
+  template <typename T>
+  __device__ __forceinline__ T operator()(T a, T b) const {
+    return a * b;
+  }
+};
+struct MulZero {
+  template <typename T>
+  __device__ __forceinline__ T operator()(T a, T b) const {
+    return a == T(0) || b == T(0) ? T(0) : a * b;
+  }
+};
+
+// OrdChain's recursion carried one derivative further, w = 2 de/d(rho^2):
+//   g_l = a (z g_{l-1} - rho^2 w_{l-2} - 4 e_{l-2}),  w_l = z w_{l-1} + g_l.
+// p1, e1, w1 and p2: one and two degrees below.  Scaled harmonics far from the
+// origin (past reach2 of the launch's parameters) have values past the type's
+// range beside derivatives within it, and rho^2 itself may be: there mul is
+// MulZero, so that what the degree does not reach yet stays 0.
+template <typename T>
+struct HessChain {
+  T z, rho2;
+  T x = T(0);  // l - m
+  T p = T(1), p1 = T(0), p2 = T(0), d = T(0);
+  T e = T(0), e1 = T(0), f = T(0);
+  T w = T(0), w1 = T(0), g = T(0);
+  // inv: 1 / (l + m) of the next degree
+  template <typename Mul>
+  __device__ __forceinline__ void advance(T inv, Mul mul) {
+    const T a = x * inv;
+    g = mul(a, mul(z, g) - (mul(rho2, w1) + T(4) * e1));
+    w1 = w;
+    w = mul(z, w) + g;
+    f = mul(a, mul(z, f) - (mul(rho2, e1) + T(2) * p1));
+    e1 = e;
+    e = mul(z, e) + f;
+    d = mul(a, mul(z, d) - mul(rho2, p1));
+    p2 = p1;
+    p1 = p;
+    p = mul(z, p) + d;
+    x += T(1);
+  }
+};
+
 // cnt elements between LDS st[shift + j] and global g[j], where shift is g's
 // element offset from a 16-byte boundary: the aligned middle as 16-byte
 // accesses, a batch of them in flight per thread, the ends one by one.
