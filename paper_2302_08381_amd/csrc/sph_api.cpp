@@ -462,7 +462,8 @@ int32_t sph_double_backward(const void* xyz, const void* grad_Y, const void* v, 
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
-  sph::DbwdParams p{xyz, grad_Y, v, n, l_max, grad_grad_Y, grad_xyz2, ki.tile_points};
+  sph::DbwdParams p{xyz, grad_Y, v, n, l_max, grad_grad_Y, grad_xyz2, ki.tile_points,
+                    sph::scaled_reach2(l_max, dtype == SPH_F64)};
   const int64_t grid = ceil_div(n, ki.tile_points);
   if (grid > 0x7fffffff) return fail(SPH_ERR_INVALID, "n too large for one launch");
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, ki.lds_bytes, &p,

@@ -2,12 +2,13 @@
 // for the outputs): one lane per (point, order), see sph_ord.inl.
 //
 // A lane walks the degrees upward at fixed order with the recursion carried to
-// second derivatives, as in sph_hess.inl, and its sums over the degrees are of
+// second derivatives (HessChain), and its sums over the degrees are of
 // gY times the few quantities that depend on the degree (q, T, Z, W, V, U and
 // four more weighted by l); the order's factors, v and u enter once, after the
 // last degree.  ggY takes gY's place in the LDS tile.  Where a sum is not
 // finite the lane forms its columns' H v one by one instead, so that an
-// infinite gY gives its products with them.
+// infinite gY gives its products with them; and where the scaled harmonics may
+// be past the type's range (see HessChain) its columns of ggY as well.
 //
 // Against one lane per point with groups of degrees staged through LDS: float
 // l_max 16, 100 000 points 442 -> 88 us, l_max 32 1769 -> 267 (3.3 TB/s);
@@ -175,16 +176,18 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
     const T rho2 = static_cast<T>(ux * ux + uy * uy);
     const T vx = v0 * ir, vy = v1 * ir, vz = v2 * ir;
     const T rho = x * vx + y * vy, uv = rho + z * vz;
-    const T tvp = tpx * vx + tpy * vy, tvm = tmx * vx + tmy * vy;
+    T tvp = tpx * vx + tpy * vy, tvm = tmx * vx + tmy * vy;
     // H(c_m) v and H(s_m) v
-    const T hpx = A * vx - B * vy, hpy = -(B * vx + A * vy);
-    const T hmx = B * vx + A * vy, hmy = A * vx - B * vy;
+    T hpx = A * vx - B * vy, hpy = -(B * vx + A * vy);
+    T hmx = B * vx + A * vy, hmy = A * vx - B * vy;
+    if (mm == 0) tvp = tvm = hpx = hpy = hmx = hmy = T(0);  // (also of an infinite v)
+    const bool far = !NORM && !(rho2 + z * z <= static_cast<T>(P.reach2));
     __syncthreads();
     const int kb = l0 * l0 + l0;
     T* basp = st + hg + p * S + kb + mm;
     T* basm = basp - 2 * mm;
     T fl = T(l0);
-    T fx = T(0), pv = T(1), p1 = T(0), p2 = T(0), d = T(0), e = T(0), e1 = T(0), f = T(0), w = T(0), w1 = T(0), g = T(0);
+    HessChain<T> ch{z, rho2};
     // sums over the degrees, per sign: of gY times q, T, Z, W, V, U and, for
     // the normalised harmonics, l q, l(l+2) q, l T, l Z
     T Sq[2] = {}, Sl[2] = {}, Sll[2] = {}, St[2] = {}, Slt[2] = {}, Sz[2] = {}, Slz[2] = {}, Sw[2] = {}, Sv[2] = {},
@@ -192,9 +195,9 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
     auto degree = [&](int l, T N, T inv) {
       if (lane_on && l >= mm) {
         const T gp = *basp, gm = mm == 0 ? T(0) : *basm;
-        const T q = N * pv, Tm = N * e, Wn = N * w;
-        const T Nx = N * fx;
-        const T Z = Nx * p1, V = Nx * e1, U = Nx * ((fx - T(1)) * p2);
+        const T q = N * ch.p, Tm = N * ch.e, Wn = N * ch.w;
+        const T Nx = N * ch.x;
+        const T Z = Nx * ch.p1, V = Nx * ch.e1, U = Nx * ((ch.x - T(1)) * ch.p2);
         T G = Tm * rho + Z * vz;
         if constexpr (NORM) G -= (fl * uv) * q;
         *basp = tp * G + q * tvp;
@@ -216,18 +219,7 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
         };
         sum(0, gp);
         sum(1, gm);
-        const T a = fx * inv;
-        g = a * (z * g - (rho2 * w1 + T(4) * e1));
-        w1 = w;
-        w = z * w + g;
-        f = a * (z * f - (rho2 * e1 + T(2) * p1));
-        e1 = e;
-        e = z * e + f;
-        d = a * (z * d - rho2 * p1);
-        p2 = p1;
-        p1 = pv;
-        pv = z * pv + d;
-        fx += T(1);
+        ch.advance(inv, MulPlain{});
       }
       fl += T(1);
       basp += 2 * l + 2;
@@ -273,27 +265,28 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
     };
     apply(0, tp, tpx, tpy, tvp, hpx, hpy);
     apply(1, tm, tmx, tmy, tvm, hmx, hmy);
-    if (lane_on && P.gxyz2 != nullptr) {
+    if (lane_on && (P.gxyz2 != nullptr || far)) {
       // not finite (an infinite or very large gY): column by column, so that
       // each column's product with its H v decides, not a sum's with a factor
-      if (!(hx - hx == T(0) && hy - hy == T(0) && hz - hz == T(0))) {
+      if (far || !(hx - hx == T(0) && hy - hy == T(0) && hz - hz == T(0))) {
         hx = hy = hz = T(0);
         const T* gp = gg + static_cast<int64_t>(pp) * K;
-        pv = T(1);
-        fx = p1 = p2 = d = e = e1 = f = w = w1 = g = T(0);
+        T* gt = st + hg + p * S;
+        const std::conditional_t<NORM, MulPlain, MulZero> mul;
+        ch = HessChain<T>{z, rho2};
         fl = T(mm);
 #pragma unroll 1
         for (int l = mm; l <= L; ++l) {
-          const T N = C.a[l][2 * mm], inv = C.a[l + 1][2 * mm + 1];
-          const T q = N * pv, Tm = N * e, Wn = N * w, Nx = N * fx;
-          const T Z = Nx * p1, V = Nx * e1, U = Nx * ((fx - T(1)) * p2);
-          const T gQv = Tm * rho + Z * vz, ww = Wn * rho + V * vz;
+          const T N = C.a[l][2 * mm];
+          const T q = N * ch.p, Tm = N * ch.e, Wn = N * ch.w, Nx = N * ch.x;
+          const T Z = Nx * ch.p1, V = Nx * ch.e1, U = Nx * ((ch.x - T(1)) * ch.p2);
+          const T gQv = mul(Tm, rho) + mul(Z, vz), ww = mul(Wn, rho) + mul(V, vz);
           auto col = [&](int k, T t, T tx, T ty, T tv, T Hx, T Hy) {
-            const T Yt = q * t, gx = x * Tm * t + q * tx, gy = y * Tm * t + q * ty, gz = Z * t;
-            T ax = t * (Tm * vx + x * ww) + x * Tm * tv + tx * gQv + q * Hx;
-            T ay = t * (Tm * vy + y * ww) + y * Tm * tv + ty * gQv + q * Hy;
-            T az = t * (V * rho + U * vz) + Z * tv;
+            T ax = mul(t, mul(Tm, vx) + mul(x, ww)) + mul(mul(x, Tm), tv) + mul(tx, gQv) + mul(q, Hx);
+            T ay = mul(t, mul(Tm, vy) + mul(y, ww)) + mul(mul(y, Tm), tv) + mul(ty, gQv) + mul(q, Hy);
+            T az = mul(t, mul(V, rho) + mul(U, vz)) + mul(Z, tv);
             if constexpr (NORM) {
+              const T Yt = q * t, gx = x * Tm * t + q * tx, gy = y * Tm * t + q * ty, gz = Z * t;
               const T b = fl * (gQv * t + q * tv) - fl * (fl + T(2)) * uv * Yt;
               ax -= fl * (uv * gx + Yt * vx) + b * x;
               ay -= fl * (uv * gy + Yt * vy) + b * y;
@@ -303,22 +296,12 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
             hx += a * (ax * ir);
             hy += a * (ay * ir);
             hz += a * (az * ir);
+            if (far) gt[k] = mul(t, gQv) + mul(q, tv);
           };
           const int k0 = l * l + l;
           col(k0 + mm, tp, tpx, tpy, tvp, hpx, hpy);
           if (mm > 0) col(k0 - mm, tm, tmx, tmy, tvm, hmx, hmy);
-          const T a = fx * inv;
-          g = a * (z * g - (rho2 * w1 + T(4) * e1));
-          w1 = w;
-          w = z * w + g;
-          f = a * (z * f - (rho2 * e1 + T(2) * p1));
-          e1 = e;
-          e = z * e + f;
-          d = a * (z * d - rho2 * p1);
-          p2 = p1;
-          p1 = pv;
-          pv = z * pv + d;
-          fx += T(1);
+          ch.advance(C.a[l + 1][2 * mm + 1], mul);
           fl += T(1);
         }
       } else {

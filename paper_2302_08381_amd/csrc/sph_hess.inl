@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_hess(HessParams P) {
       for (int u = 0; u < 2 * kOrdStep; ++u) Ac[u] = Bc[u];
     }
     if constexpr (!NORM) {  // past reach2: once more, see HessChain
-      if (lane_on && !(pt.rxy2 + pt.ez * pt.ez <= static_cast<T>(P.reach2))) {
+      if (lane_on && !(rho2 + z * z <= static_cast<T>(P.reach2))) {
         ch = HessChain<T>{z, rho2};
         T* o = st + sh + p * S9 + (SP == 2 && part == 1 ? -mm : mm);
         fl = T(mm);

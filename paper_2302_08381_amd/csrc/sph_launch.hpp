@@ -51,6 +51,7 @@ struct DbwdParams {
   void* ggY;   // nullable
   void* gxyz2; // nullable
   int32_t tile;  // points per block
+  double reach2; // see scaled_reach2 (k_dbord)
 };
 
 // Explicit Hessians (k_hess).

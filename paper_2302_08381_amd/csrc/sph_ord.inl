@@ -175,7 +175,9 @@ struct MulPlain {
 struct MulZero {
   template <typename T>
   __device__ __forceinline__ T operator()(T a, T b) const {
-    return a == T(0) || b == T(0) ? T(0) : a * b;
+    // one comparison of both, that is none of a loop-invariant factor alone
+    // (kept from trip to trip those spill scalar registers)
+    return fmin(fabs(a), fabs(b)) == T(0) ? T(0) : a * b;
   }
 };
 

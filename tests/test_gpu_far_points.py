@@ -40,3 +40,54 @@ def test_hessian_entries_within_range(l_max, dt):
         for l in range(l_max + 1):
             k = slice(l * l, (l + 1) ** 2)
             _check_degree(F[..., k], H[..., k], l - 2, e, dt, (l_max, e, l))
+
+
+@pytest.mark.parametrize("dt,l_max", [(torch.float32, 13), (torch.float32, 16), (torch.float32, 32), (torch.float64, 9),
+                                      (torch.float64, 12), (torch.float64, 20)])
+def test_double_backward_within_range(dt, l_max):
+    """Degrees past the compile-time ones: ggY of degree l is homogeneous of
+    degree l - 1, and gxyz2 of a gY in that degree alone of degree l - 2."""
+    import paper_2302_08381_amd as sph
+    K = (l_max + 1) ** 2
+    x = to_dev(np.asarray(BASE), dt)
+    rng = np.random.default_rng(2100 + l_max)
+    v = to_dev(rng.standard_normal((len(BASE), 3)), dt)
+    gY = to_dev(rng.standard_normal((len(BASE), K)), dt)
+    gg = sph.sph_double_backward(x, gY, v, l_max, False)[0].double().cpu().numpy()
+    for e in EXPONENTS[dt]:
+        print(f"far double backward {dt} l_max={l_max} 2^{e}", flush=True)
+        fg = sph.sph_double_backward(x * 2.0 ** e, gY, v, l_max, False)[0].double().cpu().numpy()
+        for l in range(l_max + 1):
+            _check_degree(fg[:, l * l:(l + 1) ** 2], gg[:, l * l:(l + 1) ** 2], l - 1, e, dt, (l_max, e, l))
+    # the power at which every degree's second derivatives are within the type's
+    # range and the largest degree's harmonics are past it
+    emax = torch.finfo(dt).max
+    e = int((np.log2(emax) - 16) / (l_max - 2))
+    want, size = np.zeros((len(BASE), 3)), np.zeros((len(BASE), 1))
+    for l in range(l_max + 1):
+        one = torch.zeros_like(gY)
+        one[:, l * l:(l + 1) ** 2] = gY[:, l * l:(l + 1) ** 2]
+        g2 = sph.sph_double_backward(x, one, v, l_max, False)[1].double().cpu().numpy()
+        want += np.ldexp(g2, e * (l - 2))
+        size += np.ldexp(np.abs(g2).max(1, keepdims=True), e * (l - 2))
+    got = sph.sph_double_backward(x * 2.0 ** e, gY, v, l_max, False)[1].double().cpu().numpy()
+    fits = size[:, 0] < emax * 2.0 ** -4
+    assert fits.any()
+    assert (np.abs(got - want) <= 2 * TOL[dt] * size)[fits].all(), (l_max, e, got, want)
+
+
+@pytest.mark.parametrize("axis", [0, 2])
+@pytest.mark.parametrize("dt,l_max", [(torch.float32, 12), (torch.float32, 13), (torch.float64, 8), (torch.float64, 9)])
+def test_double_backward_of_infinite_v(dt, l_max, axis):
+    """The columns of order 0, whose factor has no gradient, take an infinite v
+    to the infinity of their derivative's sign."""
+    import paper_2302_08381_amd as sph
+    x = to_dev(np.asarray([[0.3, 0.2, 0.7], [-0.5, 0.1, 0.4]]), dt)
+    v = torch.zeros_like(x)
+    v[:, axis] = float("inf")
+    gY = torch.ones((2, (l_max + 1) ** 2), dtype=dt, device="cuda")
+    gg = sph.sph_double_backward(x, gY, v, l_max, False)[0]
+    d = sph.sph_compute_with_gradients(x, l_max, False)[1][:, axis]
+    for l in range(1 if axis == 2 else 2, l_max + 1):  # (degree 1 has no derivative along x at order 0)
+        k = l * l + l
+        assert torch.equal(gg[:, k], torch.sign(d[:, k]) * float("inf")), (l, gg[:, k], d[:, k])
