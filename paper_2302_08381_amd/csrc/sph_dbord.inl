@@ -26,7 +26,7 @@ __host__ __device__ constexpr int dbord_stride(int L) { return (L + 1) * (L + 1)
 
 template <typename T>
 __host__ __device__ constexpr size_t dbord_lds_bytes(int L, int points) {
-  return sizeof(T) * (static_cast<size_t>(ord_block<T>(points * dbord_stride(L))) + 3u * (L + 1) * points);
+  return sizeof(T) * (static_cast<size_t>(ord_block<T>(points * dbord_stride(L))) + (3u * (L + 1) + 1u) * points);
 }
 
 // cnt elements of rows of K between global g and LDS rows of K + 1 (K a whole
@@ -105,6 +105,7 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
   const int PT = P.tile;
   T* st = reinterpret_cast<T*>(smem);
   T* sacc = st + ord_block<T>(PT * S);
+  T* sir = sacc + 3 * (L + 1) * PT;  // 1/r of each point
   const int tid = threadIdx.x, nt = blockDim.x;
   const OrdTable<T>& C = ord_table<T>(0);
   const int m = tid / PT, p = tid - m * PT;
@@ -293,9 +294,9 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
               az -= fl * (uv * gz + Yt * vz) + b * z;
             }
             const T a = gp[k];
-            hx += a * (ax * ir);
-            hy += a * (ay * ir);
-            hz += a * (az * ir);
+            hx += a * ax;
+            hy += a * ay;
+            hz += a * az;
             if (far) gt[k] = mul(t, gQv) + mul(q, tv);
           };
           const int k0 = l * l + l;
@@ -304,11 +305,8 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
           ch.advance(C.a[l + 1][2 * mm + 1], mul);
           fl += T(1);
         }
-      } else {
-        hx *= ir;
-        hy *= ir;
-        hz *= ir;
       }
+      if (m == 0) sir[p] = ir;
       sacc[m * PT + p] = hx;
       sacc[(L + 1 + m) * PT + p] = hy;
       sacc[(2 * (L + 1) + m) * PT + p] = hz;
@@ -320,7 +318,9 @@ __global__ __launch_bounds__(256) void k_dbord(DbwdParams P) {
         const T* sp = sacc + a * (L + 1) * PT + q;
         T s = T(0);
         for (int j = 0; j <= L; ++j) s += sp[j * PT];
-        static_cast<T*>(P.gxyz2)[(p0 + q) * 3 + a] = s;
+        // the second 1/r last: a sum that it takes past the type's range is an
+        // infinity, not the difference of the orders' infinities
+        static_cast<T*>(P.gxyz2)[(p0 + q) * 3 + a] = s * sir[q];
       }
     }
     if (P.ggY != nullptr) {

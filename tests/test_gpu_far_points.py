@@ -91,3 +91,21 @@ def test_double_backward_of_infinite_v(dt, l_max, axis):
     for l in range(1 if axis == 2 else 2, l_max + 1):  # (degree 1 has no derivative along x at order 0)
         k = l * l + l
         assert torch.equal(gg[:, k], torch.sign(d[:, k]) * float("inf")), (l, gg[:, k], d[:, k])
+
+
+@pytest.mark.parametrize("dt,l_max", [(torch.float32, 12), (torch.float32, 13), (torch.float32, 32), (torch.float64, 8),
+                                      (torch.float64, 9)])
+def test_double_backward_next_to_the_origin(dt, l_max):
+    """gxyz2 of the normalised harmonics, homogeneous of degree -2, past the
+    type's range: the infinity of its sign."""
+    import paper_2302_08381_amd as sph
+    rng = np.random.default_rng(2200 + l_max)
+    x = to_dev(rng.uniform(0.25, 1.0, (40, 3)) * rng.choice([-1.0, 1.0], (40, 3)), dt)
+    v = to_dev(rng.standard_normal((40, 3)), dt)
+    gY = to_dev(rng.standard_normal((40, (l_max + 1) ** 2)), dt)
+    e = {torch.float32: -70, torch.float64: -530}[dt]
+    base = sph.sph_double_backward(x, gY, v, l_max, True)[1]
+    got = sph.sph_double_backward(x * 2.0 ** e, gY, v, l_max, True)[1]
+    big = base.abs() > 2.0  # times 2^140 or 2^1060; far above the errors of either
+    assert int(big.sum()) > 60
+    assert torch.equal(got[big], torch.sign(base[big]) * float("inf"))
