@@ -247,7 +247,10 @@ int32_t sph_e3nn_vector_jacobian(const void* xyz_p, const void* grad_Y, int64_t 
  * its default tile, the same on a 16-point tile, the
  * run-time-degree kernel, the 16-point tile with its degrees split between
  * two waves, and for l_max <= 3 the kernel with one lane per point) crossed
- * with every persistent-grid size.
+ * with every persistent-grid size; past the unrolled kernels (float l_max >
+ * 12, double l_max > 8) the default kernel alone, so that Y and dY there are
+ * those of sph_compute_with_gradients bit by bit unless sph_batched_set_config
+ * (or a cached choice) names another.
  *   xyz        in  [n_points,3]
  *   offsets    in  int64 [n_env+1], DEVICE memory
  *   n_env      number of environments (>= 0)
@@ -355,7 +358,9 @@ int32_t sph_batched_get_config(int32_t l_max, int32_t normalize, int32_t dtype,
  * runtime_degree for every l_max, degree_split for float 9 <= l_max <= 12,
  * double 4 <= l_max <= 8 and, without the backward, every larger l_max;
  * one_lane for l_max <= 3; a variant may name the default kernel.  Values
- * only: runtime_degree where the default is unrolled.
+ * only: runtime_degree where the default is unrolled.  Past the unrolled
+ * kernels runtime_degree and degree_split are another recursion than the
+ * default: other roundings, and up to three times its error (float l_max 32).
  */
 int32_t sph_batched_set_config(int32_t l_max, int32_t normalize, int32_t dtype,
                                int32_t store_dY, int32_t with_backward,

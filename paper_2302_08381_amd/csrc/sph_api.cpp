@@ -266,7 +266,10 @@ unsigned batched_grid(const sph::KernelInfo& ki, int64_t n, int bpc) {
 
 // Times every kernel variant of the combination with every persistent-grid
 // size on the caller's buffers (the kernel is a pure function of its inputs,
-// so repeated runs leave the right result) and returns the fastest.
+// so repeated runs leave the right result) and returns the fastest.  Past the
+// compile-time degrees only the default's grids: the other variants are other
+// recursions there, whose larger errors no timing should choose (and k_ord was
+// the fastest in all of 144 combinations of type, l_max and outputs).
 // Synchronises the host.
 Choice autotune(int32_t dtype, int L, int norm, bool store_dy, bool fused, sph::FwdParams params,
                 hipStream_t s) {
@@ -279,7 +282,9 @@ Choice autotune(int32_t dtype, int L, int norm, bool store_dy, bool fused, sph::
     return best;
   }
   const void* tried[sph::kNumFwdVariants] = {};
+  const bool past = L > (dtype == SPH_F64 ? sph::kCompileMax<double> : sph::kCompileMax<float>);
   for (int v = 0; v < sph::kNumFwdVariants; ++v) {
+    if (past && v != sph::kVarDefault) continue;
     const sph::KernelInfo ki = fwd_info(dtype, L, norm, store_dy, fused, v);
     if (ki.fn == nullptr) continue;
     bool seen = false;  // two variants may name one kernel
