@@ -129,6 +129,27 @@ __device__ __forceinline__ int64_t group_share(const int64_t* o, int64_t n_env, 
   return lo;
 }
 
+// The environments [e, e_end) of block blockIdx.x, the same for every wave.  A
+// grid of at least n_env blocks takes one each, without the search's chain of
+// dependent loads (float, 8 channels l_max 3, 250 environments of 68 points:
+// 7.4 us with it, 4.8 without; backward 10.9 and 7.8); eight neighbours change places from one eight
+// to the next, so that a pattern of empty ones does not leave XCDs (which
+// blocks go to in turn) without work.  A smaller grid takes shares, each wave
+// finding both ends at once, lanes 0..31 the first, 32..63 the last.
+__device__ __forceinline__ void block_share(const int64_t* o, int64_t n_env, int64_t n, int lane, int64_t& e,
+                                            int64_t& e_end) {
+  const int64_t G = gridDim.x, g = blockIdx.x;
+  if (G >= n_env) {
+    e = g < G / kNumXcd * kNumXcd ? g / kNumXcd * kNumXcd + (g + g / kNumXcd) % kNumXcd : g;
+    e_end = e < n_env ? e + 1 : e;
+    return;
+  }
+  const int half = lane / 32;
+  const int64_t bound = group_share(o, n_env, n, g + half, G, lane % 32, half * 32, 32);
+  e = uniform64(__shfl(bound, 0));
+  e_end = g + 1 == G ? n_env : uniform64(__shfl(bound, 32));
+}
+
 // Values of degrees [la, lb) of one point into its LDS row.  LT >= 0: the
 // degree loop is unrolled to LT with compile-time degrees (each row's
 // coefficients fold to literals), every row behind a uniform range check;

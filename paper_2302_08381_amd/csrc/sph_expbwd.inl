@@ -232,16 +232,8 @@ __global__ __launch_bounds__(kWave * DS) __attribute__((amdgpu_waves_per_eu(expb
     if (lane == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // Block g of G takes share g of the environments (group_share); each wave
-  // finds both ends at once, lanes 0..31 the first, 32..63 the last.
-  const int64_t G = gridDim.x, g = blockIdx.x;
-  int64_t e, e_end;
-  {
-    const int half = lane / 32;
-    const int64_t bound = group_share(P.offsets, P.n_env, P.n, g + half, G, lane % 32, half * 32, 32);
-    e = uniform64(__shfl(bound, 0));
-    e_end = g + 1 == G ? P.n_env : uniform64(__shfl(bound, 32));
-  }
+  int64_t e, e_end;  // this block's environments
+  block_share(P.offsets, P.n_env, P.n, lane, e, e_end);
   if (e >= e_end) return;
   // offsets clamped into [0, n], so that inconsistent ones (reported through
   // the status word) never index out of bounds

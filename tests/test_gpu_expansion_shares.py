@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+from workloads import standard_normal
+
 from _gpu_common import host_points, to_dev
-from test_gpu_expansion import _case, _check
+from test_gpu_expansion import _case, _check, _check_backward
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +54,41 @@ def test_empty_environments_are_spread(where, l_max, n_max):
         kept = np.concatenate([[0], np.cumsum(counts[full])])
         _check(c[torch.as_tensor(full, device="cuda")], host_points(xyz), kept, Rt.cpu().double().numpy(), l_max, True,
                torch.float32, where)
+
+
+# both sides of the counts of environments at which the waves change (512 is
+# two a CU), and of eight
+@pytest.mark.parametrize("n_env", [1, 2, 7, 8, 9, 17, 511, 512, 513, 600])
+@pytest.mark.parametrize("dt,l_max,n_max", [(torch.float32, 3, 8), (torch.float32, 4, 5), (torch.float64, 3, 16),
+                                            (torch.float64, 1, 12), (torch.float64, 4, 5), (torch.float64, 4, 8),
+                                            (torch.float64, 5, 8), (torch.float64, 5, 7)])
+def test_shares_of_few_environments(dt, l_max, n_max, n_env):
+    import paper_2302_08381_amd as sph
+    print(f"expansion shares {n_env} {dt} l_max={l_max} n_max={n_max}", flush=True)
+    counts = np.arange(n_env) * 7 % 5  # 0 .. 4 points
+    counts[0] = 70
+    pts, offs, R = _case(counts, l_max, n_max, 1950 + n_env)
+    xyz, Rt, o = to_dev(pts, dt), to_dev(R, dt), torch.as_tensor(offs, device="cuda")
+    c = torch.full((n_env, n_max, (l_max + 1) ** 2), float("nan"), dtype=dt, device="cuda")
+    sph.sph_radial_expansion(xyz, o, Rt, l_max, out=c)
+    hp, hR = host_points(xyz), Rt.cpu().double().numpy()
+    _check(c, hp, offs, hR, l_max, True, dt, f"{n_env}")
+    G = to_dev(standard_normal(tuple(c.shape), 1951), dt)
+    gx, gR = sph.sph_radial_expansion_backward(xyz, o, Rt, G, l_max, True)
+    _check_backward(gx, gR, hp, offs, hR, G.cpu().double().numpy(), l_max, True, dt, f"{n_env}")
+
+
+@pytest.mark.parametrize("per", [127, 128])
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64])
+def test_long_environments_past_two_a_cu(dt, per):
+    """The length from which four waves take environments that are resident at
+    once, and the one below it."""
+    import paper_2302_08381_amd as sph
+    n_env, l_max, n_max = 520, 3, 8
+    pts, offs, R = _case([per] * n_env, l_max, n_max, 1960)
+    xyz, Rt = to_dev(pts, dt), to_dev(R, dt)
+    c = sph.sph_radial_expansion(xyz, torch.as_tensor(offs, device="cuda"), Rt, l_max)
+    hp, hR = host_points(xyz), Rt.cpu().double().numpy()
+    for e in (0, 259, 512, 519):  # the grid's environments one by one
+        b = slice(offs[e], offs[e + 1])
+        _check(c[e:e + 1], hp[b], np.array([0, per]), hR[b], l_max, True, dt, f"environment {e}")
