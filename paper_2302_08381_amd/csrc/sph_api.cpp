@@ -580,8 +580,11 @@ int32_t sph_radial_expansion(const void* xyz, const int64_t* offsets, int64_t n_
                               {status, status ? size_t(4) : size_t(0), "status"}})) != SPH_OK)
     return st;
   const bool aligned = reinterpret_cast<uintptr_t>(R) % 16 == 0;
-  const sph::KernelInfo ki = dtype == SPH_F64 ? sph::expand_info_f64(l_max, normalize, n_max, aligned, n_env)
-                                              : sph::expand_info_f32(l_max, normalize, n_max, aligned, n_env);
+  auto info = [&](bool two) {
+    return dtype == SPH_F64 ? sph::expand_info_f64(l_max, normalize, n_max, aligned, two)
+                            : sph::expand_info_f32(l_max, normalize, n_max, aligned, two);
+  };
+  sph::KernelInfo ki = info(false);
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   // Where the kernel has no LDS size of its own: the largest chunk (points per
   // LDS tile) within 64 KiB, two blocks per CU; else an 8-point chunk within
@@ -592,13 +595,24 @@ int32_t sph_radial_expansion(const void* xyz, const int64_t* offsets, int64_t n_
   };
   int chunk = 128;
   while (chunk > 8 && lds_of(chunk) > 64 * 1024) chunk /= 2;
-  const size_t lds = ki.lds_bytes != 0 ? ki.lds_bytes : lds_of(chunk);
+  size_t lds = ki.lds_bytes != 0 ? ki.lds_bytes : lds_of(chunk);
   if (lds > 160 * 1024) return fail(SPH_ERR_INVALID, "l_max and n_max need more LDS than one block has");
   hipError_t e = ensure_lds(ki.fn, lds);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
+  const int cus = num_cus();
+  int64_t resident = static_cast<int64_t>(cus) * resident_per_cu(ki.fn, ki.block, lds);
+  if (sph::expfwd_on_two(l_max, n_max) && sph::expfwd_two_waves(n_points, n_env, resident, cus)) {
+    ki = info(true);
+    lds = ki.lds_bytes;
+    e = ensure_lds(ki.fn, lds);
+    if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute");
+    resident = static_cast<int64_t>(cus) * resident_per_cu(ki.fn, ki.block, lds);
+  }
   sph::ExpandParams p{xyz, R, offsets, n_env, n_points, l_max, n_max, chunk, c, status};
-  // a resident grid: each block walks its environments as a pipeline
-  const int64_t resident = static_cast<int64_t>(num_cus()) * resident_per_cu(ki.fn, ki.block, lds);
+  // a resident grid: each block walks its environments as a pipeline.  (More
+  // blocks, one for each of up to 1.5 times as many environments, start the
+  // last as the first end, 15.6 -> 14.6 us for float 7 channels l_max 3, 2000
+  // environments of 68 points, but where every second is empty 10.5 -> 15.2.)
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(n_env, std::max<int64_t>(resident, 1)));
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, lds, &p, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "radial expansion launch");

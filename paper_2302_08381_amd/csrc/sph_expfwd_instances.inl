@@ -41,7 +41,7 @@ constexpr int layout_of(int L, int n_max) {
 template <int LT, int I, int WV, bool VEC>
 KernelInfo info() {
   constexpr int CW = layout_cw(I), NG = layout_ng(I);
-  if constexpr (!layout_serves(LT, I) || (WV == 2 && expfwd_waves(LT, CW * NG, 1 << 20) != 2)) {
+  if constexpr (!layout_serves(LT, I) || (WV == 2 && !expfwd_on_two(LT, CW * NG))) {
     return KernelInfo{nullptr, 0, 0, 0, 0};
   } else {
     return KernelInfo{reinterpret_cast<const void*>(&k_expfwd<T, LT, SPH_NORM != 0, CW, NG, WV, VEC>),
@@ -77,11 +77,11 @@ struct Tables {
 
 }  // namespace
 
-KernelInfo SPH_CAT(SPH_CAT(SPH_CAT(expfwd_info_, SPH_SUFFIX), _n), SPH_NORM)(int L, int n_max, bool aligned, int64_t n_env) {
+KernelInfo SPH_CAT(SPH_CAT(SPH_CAT(expfwd_info_, SPH_SUFFIX), _n), SPH_NORM)(int L, int n_max, bool aligned, bool two) {
   static const Tables t;
   const int i = layout_of(L, n_max);
   const bool vec = aligned && n_max == layout_cw(i) * layout_ng(i);
-  return t.k[i][expfwd_waves(L, n_max, n_env) == 2 ? 1 : 0][vec ? 1 : 0][L];
+  return t.k[i][two && expfwd_on_two(L, n_max) ? 1 : 0][vec ? 1 : 0][L];
 }
 
 }  // namespace sph

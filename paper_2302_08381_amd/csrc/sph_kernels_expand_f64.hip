@@ -77,10 +77,10 @@ const Tables& tables() {
 
 }  // namespace
 
-KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n_env) {
+KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, bool two) {
   if (L < 0 || L > kMaxLmax || (normalize != 0 && normalize != 1) || n_max < 1) return KernelInfo{nullptr, 0, 0, 0, 0};
   if (expfwd_serves(L, n_max))
-    return normalize ? expfwd_info_f64_n1(L, n_max, aligned, n_env) : expfwd_info_f64_n0(L, n_max, aligned, n_env);
+    return normalize ? expfwd_info_f64_n1(L, n_max, aligned, two) : expfwd_info_f64_n0(L, n_max, aligned, two);
   const Tables& t = tables();
   const int a = expand_acc(L, n_max) == 8 ? 1 : 0;
   const void* fn = L <= kSpecMax ? t.spec[normalize][a][L] : t.fn[normalize][a][bucket_index(L)];

@@ -119,13 +119,20 @@ __host__ __device__ constexpr size_t expand_lds_bytes(int L, int n_max, int chun
 constexpr int kExpandMaxL = 12;
 constexpr int kExpFwdChannels = 16;
 constexpr bool expfwd_serves(int L, int n_max) { return L <= kExpandMaxL && n_max <= kExpFwdChannels; }
-// Its waves.  Up to l_max 4 two, whose blocks are more numerous (8 channels,
-// 20 000 environments of 68 points, two / four waves: float l_max 4 55 / 65
-// us, l_max 6 91 / 87, double l_max 4 112 / 161), unless the environments
-// leave CUs without a second block (float l_max 4: 10 environments of 20 000
-// points 525 / 430 us, 300 of 600 21 / 18, 700 of 600 23 / 22) or there are
-// more channels (12, float l_max 4: 83 / 80).
-constexpr int expfwd_waves(int L, int n_max, int64_t n_env) { return L <= 4 && n_max <= 8 && n_env > 512 ? 2 : 4; }
+// Up to l_max 4 and 8 channels it exists on two waves as well as four, see
+// expfwd_two_waves for the choice (12 channels, float l_max 4, 20 000
+// environments: 83 us on two, 80 on four).
+constexpr bool expfwd_on_two(int L, int n_max) { return L <= 4 && n_max <= 8; }
+// Two waves, whose blocks are more numerous, where there are more environments
+// than four-wave blocks are resident (two / four waves, 8 channels, 20 000
+// environments of 68 points: float l_max 4 57 / 67 us, double l_max 4 117 /
+// 166; 2000 of 68, float l_max 3 8.1 / 13.4), and where the environments are
+// short and fill the CUs twice (1000 of 16, double l_max 4 7.4 / 10.5).
+// Long environments that are resident at once are four waves' (700 of 600,
+// float l_max 3 21.4 / 19.3, 5 channels 27.8 / 23.1).
+constexpr bool expfwd_two_waves(int64_t n, int64_t n_env, int64_t resident4, int cus) {
+  return n_env > resident4 || (n_env > 2 * cus && n < 128 * n_env);
+}
 
 // Backward of the radial expansion (k_expand_bwd).
 struct ExpandBwdParams {
@@ -272,12 +279,13 @@ KernelInfo hess_info_f64(int L, int normalize);
 // L <= 12 and double L <= 8, the m-extent bucket of L past them, with the
 // accumulator width expand_acc(L, n_max), block = 128 threads and lds_bytes
 // left 0 (they depend on n_max and the chunk, see expand_lds_bytes).
-KernelInfo expand_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n_env);
-KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n_env);
-KernelInfo expfwd_info_f32_n0(int L, int n_max, bool aligned, int64_t n_env);
-KernelInfo expfwd_info_f32_n1(int L, int n_max, bool aligned, int64_t n_env);
-KernelInfo expfwd_info_f64_n0(int L, int n_max, bool aligned, int64_t n_env);
-KernelInfo expfwd_info_f64_n1(int L, int n_max, bool aligned, int64_t n_env);
+// two: on two waves (expfwd_on_two).
+KernelInfo expand_info_f32(int L, int normalize, int n_max, bool aligned, bool two);
+KernelInfo expand_info_f64(int L, int normalize, int n_max, bool aligned, bool two);
+KernelInfo expfwd_info_f32_n0(int L, int n_max, bool aligned, bool two);
+KernelInfo expfwd_info_f32_n1(int L, int n_max, bool aligned, bool two);
+KernelInfo expfwd_info_f64_n0(int L, int n_max, bool aligned, bool two);
+KernelInfo expfwd_info_f64_n1(int L, int n_max, bool aligned, bool two);
 // Its backward: channels padded to 8 or 16 (n_max <= 16); aligned: R and
 // grad_R start on 16-byte boundaries; slices: the G slices of a block.
 KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);
