@@ -644,8 +644,10 @@ int32_t sph_radial_expansion_backward(const void* xyz, const int64_t* offsets, i
                               {grad_R, un * nr * w, "grad_R"}, {status, sb, "status"}})) != SPH_OK)
     return st;
   const bool aligned = (reinterpret_cast<uintptr_t>(R) | reinterpret_cast<uintptr_t>(grad_R)) % 16 == 0;
-  const sph::KernelInfo ki = dtype == SPH_F64 ? sph::expand_bwd_info_f64(l_max, normalize, n_max, aligned, n_points, n_env)
-                                              : sph::expand_bwd_info_f32(l_max, normalize, n_max, aligned, n_points, n_env);
+  const int cus = num_cus();
+  const sph::KernelInfo ki = dtype == SPH_F64
+                                 ? sph::expand_bwd_info_f64(l_max, normalize, n_max, aligned, n_points, n_env, cus)
+                                 : sph::expand_bwd_info_f32(l_max, normalize, n_max, aligned, n_points, n_env, cus);
   if (ki.fn == nullptr) return fail(SPH_ERR_INVALID, "no kernel for these arguments");
   if (ki.lds_bytes > 160 * 1024) return fail(SPH_ERR_INVALID, "l_max and n_max need more LDS than one block has");
   hipError_t e = ensure_lds(ki.fn, ki.lds_bytes);
@@ -653,9 +655,8 @@ int32_t sph_radial_expansion_backward(const void* xyz, const int64_t* offsets, i
   sph::ExpandBwdParams p{xyz, R, offsets, n_env, n_points, l_max, n_max, grad_c, grad_xyz, grad_R, status,
                          ki.slices};
   // a resident grid, each block walking its own environments
-  const int64_t resident = static_cast<int64_t>(num_cus()) * resident_per_cu(ki.fn, ki.block, ki.lds_bytes);
-  const int64_t grid =
-      std::max<int64_t>(1, std::min<int64_t>(n_env, std::max<int64_t>(resident, 1)));
+  const int64_t resident = static_cast<int64_t>(cus) * resident_per_cu(ki.fn, ki.block, ki.lds_bytes);
+  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(n_env, std::max<int64_t>(resident, 1)));
   e = launch(ki.fn, static_cast<unsigned>(grid), ki.block, ki.lds_bytes, &p, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "radial expansion backward launch");
   return ok();

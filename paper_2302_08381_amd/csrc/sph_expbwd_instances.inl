@@ -13,37 +13,41 @@ namespace {
 using T = SPH_T;
 constexpr int kSlots = kExpandMaxL + 1;
 
-template <int LT, int NPC, bool VEC>
+template <int LT, int NPC, bool VEC, bool FEW>
 const void* fn_ptr() {
   if constexpr (!expbwd_serves<T>(LT, NPC))
     return nullptr;
   else
-    return reinterpret_cast<const void*>(&k_expbwd<T, LT, SPH_NORM != 0, NPC, expbwd_waves<T>(LT, NPC),
+    return reinterpret_cast<const void*>(&k_expbwd<T, LT, SPH_NORM != 0, NPC, expbwd_waves<T>(LT, NPC, VEC, FEW),
                                                  VEC && expbwd_vec<T>(LT, NPC)>);
 }
 
-template <int NPC, bool VEC, int... Ls>
+template <int NPC, bool VEC, bool FEW, int... Ls>
 void fill(const void** out, std::integer_sequence<int, Ls...>) {
-  const void* tbl[] = {fn_ptr<Ls, NPC, VEC>()...};
+  const void* tbl[] = {fn_ptr<Ls, NPC, VEC, FEW>()...};
   for (size_t i = 0; i < sizeof...(Ls); ++i) out[i] = tbl[i];
 }
 
 struct Tables {
-  const void* fn[2][2][kSlots];  // [16 channels][whole vectors]
+  const void* fn[2][2][2][kSlots];  // [few environments][16 channels][whole vectors]
   Tables() {
     using Ls = std::make_integer_sequence<int, kSlots>;
-    fill<8, false>(fn[0][0], Ls{});
-    fill<8, true>(fn[0][1], Ls{});
-    fill<16, false>(fn[1][0], Ls{});
-    fill<16, true>(fn[1][1], Ls{});
+    fill<8, false, false>(fn[0][0][0], Ls{});
+    fill<8, true, false>(fn[0][0][1], Ls{});
+    fill<16, false, false>(fn[0][1][0], Ls{});
+    fill<16, true, false>(fn[0][1][1], Ls{});
+    fill<8, false, true>(fn[1][0][0], Ls{});
+    fill<8, true, true>(fn[1][0][1], Ls{});
+    fill<16, false, true>(fn[1][1][0], Ls{});
+    fill<16, true, true>(fn[1][1][1], Ls{});
   }
 };
 
 }  // namespace
 
-const void* SPH_CAT(SPH_CAT(SPH_CAT(expbwd_fn_, SPH_SUFFIX), _n), SPH_NORM)(int L, int npc, bool vec) {
+const void* SPH_CAT(SPH_CAT(SPH_CAT(expbwd_fn_, SPH_SUFFIX), _n), SPH_NORM)(int L, int npc, bool vec, bool few) {
   static const Tables t;
-  return L < 0 || L > kExpandMaxL ? nullptr : t.fn[npc == 16 ? 1 : 0][vec ? 1 : 0][L];
+  return L < 0 || L > kExpandMaxL ? nullptr : t.fn[few ? 1 : 0][npc == 16 ? 1 : 0][vec ? 1 : 0][L];
 }
 
 }  // namespace sph

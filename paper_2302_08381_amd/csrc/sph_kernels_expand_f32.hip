@@ -87,14 +87,15 @@ KernelInfo expand_info_f32(int L, int normalize, int n_max, bool aligned, bool t
   return KernelInfo{fn, 0, 0, 0, kExpandThreads};
 }
 
-KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env) {
+KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env, int cus) {
   if (L < 0 || L > kMaxLmax || (normalize != 0 && normalize != 1) || n_max < 1 || n_max > 16)
     return KernelInfo{nullptr, 0, 0, 0, 0};
   const int npc = n_max > 8 ? 16 : 8;
   if (expbwd_serves<T>(L, npc)) {
     const bool vec = n_max == npc && aligned;
-    const void* fn = normalize ? expbwd_fn_f32_n1(L, npc, vec) : expbwd_fn_f32_n0(L, npc, vec);
-    const int waves = expbwd_waves<T>(L, npc);
+    const bool few = n_env <= 2 * cus;
+    const void* fn = normalize ? expbwd_fn_f32_n1(L, npc, vec, few) : expbwd_fn_f32_n0(L, npc, vec, few);
+    const int waves = expbwd_waves<T>(L, npc, vec, few);
     const int slices = expbwd_slices<T>(npc, n, n_env);
     KernelInfo ki{fn, expbwd_lds_bytes<T>(L, npc, slices, waves), 0, 1, kWave * waves};
     ki.slices = slices;

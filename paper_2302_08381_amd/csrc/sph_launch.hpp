@@ -175,9 +175,20 @@ constexpr int kExpBwdSlices = 4;
 // 240, l_max 12 - / 455 / 339; 16 channels (10 000) l_max 12 - / 832 / 508.
 // Double, 8 channels l_max 3 180 / 201, l_max 8 - / 490 / 612; 3000 environments
 // l_max 10 - / 116 / 160.
+// Where it says one, two all the same
+//   for the general copies (vec: whole-vector rows) of the largest of those
+//   degrees (float 5 channels l_max 4, 5000 environments of 200 points 113 us
+//   on one, 82 on two; double l_max 5 30 % fewer);
+//   and in double, whose registers leave a SIMD one wave, for few environments
+//   (at most two a CU): 60 of 3000 points, 8 channels l_max 5 411 us on one,
+//   270 on two; 12 channels l_max 3 441 and 272, but 700 of 300 56 and 67.
 template <typename T>
-constexpr int expbwd_waves(int L, int npc) {
-  if (L <= (npc == 8 ? (sizeof(T) == 4 ? 4 : 5) : 3)) return 1;
+constexpr int expbwd_waves(int L, int npc, bool vec, bool few) {
+  if (L <= (npc == 8 ? (sizeof(T) == 4 ? 4 : 5) : 3)) {
+    if (npc == 8 && L >= 4 && !vec) return 2;
+    if (sizeof(T) == 8 && few && (npc == 16 || L == 5)) return 2;
+    return 1;
+  }
   return L >= (npc == 8 && sizeof(T) == 4 ? 12 : 11) ? 4 : 2;
 }
 // Environments per chunk: four with 8 channels (l_max 8 float 210 us against
@@ -287,15 +298,17 @@ KernelInfo expfwd_info_f32_n1(int L, int n_max, bool aligned, bool two);
 KernelInfo expfwd_info_f64_n0(int L, int n_max, bool aligned, bool two);
 KernelInfo expfwd_info_f64_n1(int L, int n_max, bool aligned, bool two);
 // Its backward: channels padded to 8 or 16 (n_max <= 16); aligned: R and
-// grad_R start on 16-byte boundaries; slices: the G slices of a block.
-KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);
-KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env);
-// The compile-time backward (L <= kCompileMax): the padded channel count npc
-// (8 or 16), with or without the whole-vector copies.
-const void* expbwd_fn_f32_n0(int L, int npc, bool vec);
-const void* expbwd_fn_f32_n1(int L, int npc, bool vec);
-const void* expbwd_fn_f64_n0(int L, int npc, bool vec);
-const void* expbwd_fn_f64_n1(int L, int npc, bool vec);
+// grad_R start on 16-byte boundaries; cus: the device's; slices: the G slices
+// of a block.
+KernelInfo expand_bwd_info_f32(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env, int cus);
+KernelInfo expand_bwd_info_f64(int L, int normalize, int n_max, bool aligned, int64_t n, int64_t n_env, int cus);
+// The compile-time backward (L <= kExpandMaxL): the padded channel count npc
+// (8 or 16), with or without the whole-vector copies, on the waves of
+// expbwd_waves.
+const void* expbwd_fn_f32_n0(int L, int npc, bool vec, bool few);
+const void* expbwd_fn_f32_n1(int L, int npc, bool vec, bool few);
+const void* expbwd_fn_f64_n0(int L, int npc, bool vec, bool few);
+const void* expbwd_fn_f64_n1(int L, int npc, bool vec, bool few);
 // e3nn's conventions: the permuted coordinates and the in-place conversion
 // of Y and dY (dtype64: double, else float).
 hipError_t e3nn_coordinates_launch(int dtype64, const void* xyz, int64_t n, void* out, hipStream_t s);
