@@ -34,10 +34,9 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 }
 
 // Copy of a radial tile from global rows [cnt][L+1][NM] (from src) into LDS
-// rows of stride RS, [L+1][NPC] each: the first `lim` channels of every row
-// (lim <= NM, NPC), the padding channels zero.  MODE 1 (NM and lim whole
-// numbers of vectors, src aligned) and 0 (else): each of the NT threads keeps
-// one slot of U channels (a vector, or one element) and walks the tile's
+// rows of stride RS, [L+1][NPC] each, the padding channels zero.  MODE 1 (NM a
+// whole number of vectors, src aligned) and 0 (else): each of the NT threads
+// keeps one slot of U channels (a vector, or one element) and walks the tile's
 // rows, a batch in flight.
 template <typename T, int NPC, int NT, int MODE>
 __device__ __forceinline__ void expand_tile_in(T* __restrict__ sR, int RS, const T* __restrict__ src, int cnt,
@@ -754,10 +753,9 @@ __device__ __forceinline__ void expand_bwd_point(const T* __restrict__ xyz, cons
 //   grad_xyz[j, a]  = sum_k gY[j, k] dY_k/dx_a(x_j),
 //                     gY[j, k] = sum_n G[e, n, k] R[j, l(k), n]
 // The run-time-degree kernel, for the degrees past k_expbwd's (and double
-// with padded 16 channels at l_max 7 and 8, see expand_bwd_info).  One lane
-// per point; neither Y nor dY is stored.  A block is one wave that walks its
-// own run of environments (an even share of the points) in chunks of 64
-// consecutive points.  A chunk may span the end of one environment and the
+// with 9..16 channels past l_max 6, see expbwd_serves).  One lane per point;
+// neither Y nor dY is stored.  A block is one wave that walks its share of the
+// environments (group_share) in chunks of 64 consecutive points.  A chunk may span the end of one environment and the
 // start of the next: the block keeps the G of both in two LDS slices
 // ([k][channel], read as 16-byte vectors) and each lane reads the slice of
 // its own point's environment.  Chunks that stopped at every environment's

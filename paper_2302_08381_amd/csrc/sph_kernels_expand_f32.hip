@@ -12,9 +12,18 @@ using T = float;
 // the m-extent bucket.
 constexpr int kSpecMax = 12;
 
+// The run-time degrees, for the buckets that reach past the compile-time ones.
+template <bool NORM, int ACC, int MM>
+const void* bucket_ptr() {
+  if constexpr (MM > kSpecMax)
+    return reinterpret_cast<const void*>(&k_expand<T, MM, -1, NORM, ACC>);
+  else
+    return nullptr;
+}
+
 template <bool NORM, int ACC, int... Is>
 void fill_expand(const void** out, std::integer_sequence<int, Is...>) {
-  const void* tbl[] = {reinterpret_cast<const void*>(&k_expand<T, kBuckets[Is], -1, NORM, ACC>)...};
+  const void* tbl[] = {bucket_ptr<NORM, ACC, kBuckets[Is]>()...};
   for (size_t i = 0; i < sizeof...(Is); ++i) out[i] = tbl[i];
 }
 
