@@ -797,8 +797,9 @@ __global__ __launch_bounds__(kWave) void k_expand_bwd(ExpandBwdParams P) {
     if (lane == 0) P.status[0] = all_ok ? 0 : 4 /* SPH_ERR_OFFSETS */;
   }
 
-  // Block g of G takes share g of the environments (group_share).  State: environment e, its range [b, t), the chunk start j0
-  // (b <= j0 < t), and which environment each G slice holds.
+  // Block g of G takes share g of the environments (group_share).  State:
+  // environment e, its range [b, t), the chunk start j0 (b <= j0 < t), and
+  // which environment each G slice holds.
   const int64_t G = gridDim.x, g = blockIdx.x;
   int64_t e = group_share(P.offsets, P.n_env, P.n, g, G, gl, 0, GS);
   const int64_t e_last = group_share(P.offsets, P.n_env, P.n, g + 1, G, gl, 0, GS);

@@ -254,7 +254,10 @@ __global__ __launch_bounds__(kWave * DS) __attribute__((amdgpu_waves_per_eu(expb
   // cnt: rows that exist past j0, at most CP
   V rv[kExpBwdBatch];
   T px = T(0), py = T(0), pz = T(0);
-  auto rows_left = [&](int64_t j) { return static_cast<int>(j_end - j < CP ? j_end - j : CP); };
+  auto rows_left = [&](int64_t j) {  // (none where inconsistent offsets end before j)
+    const int64_t d = j_end - j;
+    return static_cast<int>(d < 0 ? 0 : (d < CP ? d : CP));
+  };
   // Vectors from .. of the tile's rows in global order; vector i of the block
   // of rows is vector i % RV of LDS row i / RV, walked with running counters
   // (one division).  f(u, i, LDS element).

@@ -155,8 +155,9 @@ __global__ __launch_bounds__(kWave * WV) void k_expfwd(ExpandParams P) {
     const int64_t d = offset(i < e_end ? i : e_end) - j0;
     return static_cast<int>(d < 0 ? 0 : (d > CP ? CP + 1 : d));
   };
-  auto rows_left = [&](int64_t j) {
-    return __builtin_amdgcn_readfirstlane(static_cast<int>(j_end - j < CP ? j_end - j : CP));
+  auto rows_left = [&](int64_t j) {  // (none where inconsistent offsets end before j)
+    const int64_t d = j_end - j;
+    return __builtin_amdgcn_readfirstlane(static_cast<int>(d < 0 ? 0 : (d < CP ? d : CP)));
   };
   // The radial rows of a chunk: global [cnt][L+1][NM] to LDS rows [L+1][NP].
   // VEC (NM == NP, R 16-byte aligned): a straight copy of vectors; else
