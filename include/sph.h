@@ -146,6 +146,9 @@ int32_t sph_vector_jacobian(const void* xyz, const void* grad_Y, int64_t n, int3
  *   v              in  [n,3]  (upstream gradient of grad_xyz)
  *   grad_grad_Y    out [n,K]  (may be NULL: not computed)
  *   grad_xyz2      out [n,3]  (may be NULL: not computed)
+ * A non-finite grad_Y makes its point's grad_xyz2 infinite or NaN, which of
+ * them is not specified (the kernels add the columns in different orders);
+ * grad_grad_Y does not depend on it.
  */
 int32_t sph_double_backward(const void* xyz, const void* grad_Y, const void* v,
                             int64_t n, int32_t l_max, int32_t normalize,

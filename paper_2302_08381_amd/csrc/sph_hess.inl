@@ -23,14 +23,13 @@
 // The tile decides how many points a CU holds at once (1.8 KB each at l_max 6
 // in float), so the orders and signs are what fills its waves; a lane per row
 // of the 3x3 block forms each off-diagonal entry twice and the shared factors
-// three times (VALU 85 % busy).  Measured against that, 1e6 points: float
-// l_max 3 124 -> 106 us, l_max 6 392 -> 300 (5.9 TB/s of stores), l_max 8
-// (500 000) 511 -> 250, l_max 12 (300 000) 1242 -> 340; double l_max 4 (500
-// 000) 192 -> 158, l_max 8 (300 000) 827 -> 300; l_max 32 float (30 000) 1395
-// -> 398, double (10 000) 1156 -> 316.  What is left up to l_max 12 is close
-// to the stores, with the VALU as busy: about 98 operations per column, of
-// which the lanes below their order waste a quarter; past it the few waves
-// that the tile leaves.  Error against double, float l_max 6 / 12: 5e-7 / 6e-7
+// three times.  Measured against that, 1e6 points: float l_max 3 124 -> 106 us,
+// l_max 6 392 -> 300 (5.9 TB/s of stores), l_max 8 (500 000) 511 -> 250, l_max
+// 12 (300 000) 1242 -> 340; double l_max 4 (500 000) 192 -> 158, l_max 8 (300
+// 000) 827 -> 300; l_max 32 float (30 000) 1395 -> 398, double (10 000) 1156 ->
+// 316.  What is left up to l_max 12 is close to the stores, beside about 90
+// operations per column, of which the lanes below their order waste a quarter;
+// past it the few waves that the tile leaves.  Error against double, float l_max 6 / 12: 5e-7 / 6e-7
 // of a point's largest entry (1.6e-6 / 2e-6).
 #pragma once
 
