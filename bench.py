@@ -538,6 +538,10 @@ SUITE_COMMANDS = {
     "sq": "rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_ACTIVE_INST_VALU SQ_WAVE_CYCLES SQ_LDS_BANK_CONFLICT "
           "SQ_INSTS_LDS SQ_BUSY_CYCLES GRBM_GUI_ACTIVE --output-format csv -d {out}/suite_sq -o run -- "
           "python3 {repo}/bench.py --profile-suite --steps 2 --warmup 1",
+    "mix": "rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU_ADD_F32 SQ_INSTS_VALU_MUL_F32 SQ_INSTS_VALU_FMA_F32 "
+           "SQ_INSTS_VALU_TRANS_F32 SQ_INSTS_VALU_ADD_F64 SQ_INSTS_VALU_MUL_F64 SQ_INSTS_VALU_FMA_F64 GRBM_GUI_ACTIVE "
+           "--output-format csv -d {out}/suite_mix -o run -- "
+           "python3 {repo}/bench.py --profile-suite --steps 2 --warmup 1",
     "tcc": "rocprofv3 --pmc TCC_EA0_WRREQ_sum TCC_EA0_WRREQ_64B_sum TCC_EA0_WRREQ_LEVEL_sum GRBM_GUI_ACTIVE "
            "--output-format csv -d {out}/suite_tcc -o run -- "
            "python3 {repo}/bench.py --profile-suite --steps 2 --warmup 1",
@@ -602,8 +606,8 @@ def summarize_suite(outdir: str) -> None:
     """profiles/kernel_suite.md: per kernel of the path, its mean duration
     (kernel trace), algorithmic and HBM bytes (FETCH_SIZE / WRITE_SIZE scaled
     by the 1 GiB reference copy), and what the SQ counters say bounds it:
-    VALU instructions per wave and the share of the CUs' VALU issue slots
-    they fill, mean resident waves per CU, LDS instructions and bank-conflict
+    VALU instructions per wave, all of them and the float ones per CU and
+    cycle, mean resident waves per CU, LDS instructions and bank-conflict
     cycles.  GRBM_GUI_ACTIVE is summed over the 8 XCDs, so the kernel's
     cycles are GRBM_GUI_ACTIVE / 8; SQ_WAVE_CYCLES counts quad-cycles."""
     import csv
@@ -613,6 +617,7 @@ def summarize_suite(outdir: str) -> None:
     fetch = _per_dispatch(os.path.join(outdir, "suite_fetch", "run_counter_collection.csv"))
     write = _per_dispatch(os.path.join(outdir, "suite_write", "run_counter_collection.csv"))
     sq = _per_dispatch(os.path.join(outdir, "suite_sq", "run_counter_collection.csv"))
+    mix = _per_dispatch(os.path.join(outdir, "suite_mix", "run_counter_collection.csv"))
     tcc_path = os.path.join(outdir, "suite_tcc", "run_counter_collection.csv")
     tcc = _per_dispatch(tcc_path) if os.path.exists(tcc_path) else {}
     wait_path = os.path.join(outdir, "suite_wait", "run_counter_collection.csv")
@@ -626,11 +631,11 @@ def summarize_suite(outdir: str) -> None:
     ws = REFERENCE_COPY_BYTES / (mean_counter(write, REFERENCE_COPY, "WRITE_SIZE") * 1024)
     lines = ["# Kernel suite: time, bytes and SQ counters of every kernel of the path", "",
              "Commands (from /tmp, TMPDIR=/tmp), each in a run of its own:", ""]
-    lines += ["    " + cmds[k] for k in ("trace", "fetch", "write", "sq") + (("tcc",) if tcc else ())
+    lines += ["    " + cmds[k] for k in ("trace", "fetch", "write", "sq", "mix") + (("tcc",) if tcc else ())
               + (("wait",) if wait else ())]
     # the hash the profiled runs printed (the sources they ran), not the tree's
     run_hashes = set()
-    for k in ("trace", "fetch", "write", "sq", "tcc", "wait"):
+    for k in ("trace", "fetch", "write", "sq", "mix", "tcc", "wait"):
         log = os.path.join(outdir, f"suite_{k}.log")
         if os.path.exists(log):
             with open(log) as f:
@@ -644,13 +649,16 @@ def summarize_suite(outdir: str) -> None:
     lines += ["", f"Kernel sources hash: {run_hash}{note}", "",
               f"HBM bytes = counter KiB * 1024 * factor, the factor set so that the 1 GiB reference copy reads and "
               f"writes 1 GiB: FETCH_SIZE x{fs:.3f}, WRITE_SIZE x{ws:.3f}.  Cycles = GRBM_GUI_ACTIVE / {XCD_NUM} "
-              f"(the counter is summed over the XCDs).  VALU slots: one wave64 VALU instruction per SIMD per 4 "
-              f"cycles, i.e. one per CU per cycle over {CU_NUM} CUs.  Waves per CU: 4 * SQ_WAVE_CYCLES "
+              f"(the counter is summed over the XCDs).  Float VALU: wave64 add, multiply and fma instructions (and "
+              f"4 for each transcendental) per CU-cycle over {CU_NUM} CUs, of at most one: a SIMD takes 4 cycles for "
+              f"each (loops of independent ones reach 0.83..0.93 at 8 waves a SIMD, 0.6..0.8 at 2; double the same).  "
+              f"All VALU: the rest (integer, logic, moves, conversions) issues beside them at up to 1.55 per "
+              f"CU-cycle, so their sum is no share of a ceiling.  Waves per CU: 4 * SQ_WAVE_CYCLES "
               f"(quad-cycles) / ({CU_NUM} * cycles), of at most 32.  LDS conflict: SQ_LDS_BANK_CONFLICT cycles "
               f"per CU-cycle.", "",
               "| kernel | workload | mean us | alg. bytes | alg. GB/s | HBM bytes / alg. | VALU instr / wave | "
-              "VALU slots used | waves / CU | LDS instr / wave | LDS conflict | VGPR, AGPR | block x grid |",
-              "|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
+              "float VALU / CU-cycle | all VALU / CU-cycle | waves / CU | LDS instr / wave | LDS conflict | VGPR, AGPR | block x grid |",
+              "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for role, tag, alg, what in _suite_workloads():
         ds = sorted((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), r) for r in trace if tag in r["Kernel_Name"])
         ds = ds[-SUITE_STEPS:]
@@ -663,10 +671,14 @@ def summarize_suite(outdir: str) -> None:
         c = {n: mean_counter(sq, tag, n) for n in ("SQ_WAVES", "SQ_INSTS_VALU", "SQ_WAVE_CYCLES", "SQ_INSTS_LDS",
                                                   "SQ_LDS_BANK_CONFLICT", "GRBM_GUI_ACTIVE")}
         cyc = c["GRBM_GUI_ACTIVE"] / XCD_NUM
+        m = {n: mean_counter(mix, tag, f"SQ_INSTS_VALU_{n}")
+             for n in ("ADD_F32", "MUL_F32", "FMA_F32", "ADD_F64", "MUL_F64", "FMA_F64", "TRANS_F32")}
+        flt = sum(m.values()) + 3 * m["TRANS_F32"]
+        mix_cyc = mean_counter(mix, tag, "GRBM_GUI_ACTIVE") / XCD_NUM
         lines.append(
             f"| {role} (`{row['Kernel_Name'].split('(')[0].replace('void sph::', '')}`) | {what} | {mean * 1e6:.1f} | "
             f"{alg:.4g} | {alg / mean / 1e9:.0f} | {hbm / alg:.3f} | {c['SQ_INSTS_VALU'] / c['SQ_WAVES']:.0f} | "
-            f"{100 * c['SQ_INSTS_VALU'] / (CU_NUM * cyc):.0f} % | {4 * c['SQ_WAVE_CYCLES'] / (CU_NUM * cyc):.1f} | "
+            f"{flt / (CU_NUM * mix_cyc):.2f} | {c['SQ_INSTS_VALU'] / (CU_NUM * cyc):.2f} | {4 * c['SQ_WAVE_CYCLES'] / (CU_NUM * cyc):.1f} | "
             f"{c['SQ_INSTS_LDS'] / c['SQ_WAVES']:.0f} | {100 * c['SQ_LDS_BANK_CONFLICT'] / (CU_NUM * cyc):.1f} % | "
             f"{row['VGPR_Count']}, {row['Accum_VGPR_Count']} | {row['Workgroup_Size_X']} x "
             f"{int(row['Grid_Size_X']) // max(1, int(row['Workgroup_Size_X']))} |")
