@@ -21,7 +21,8 @@ class _SphBackward(torch.autograd.Function):
         ctx.save_for_backward(grad_Y, xyz)
         ctx.l_max = l_max
         ctx.normalize = normalize
-        return _native.sph_vector_jacobian(xyz, grad_Y.contiguous(), l_max, normalize)
+        # (contiguous: as saved, unless saved-tensor hooks gave another layout back)
+        return _native.sph_vector_jacobian(xyz.contiguous(), grad_Y.contiguous(), l_max, normalize)
 
     @staticmethod
     def backward(ctx, v):
@@ -30,7 +31,7 @@ class _SphBackward(torch.autograd.Function):
         want_x = ctx.needs_input_grad[1]
         if not (want_gg or want_x):
             return None, None, None, None
-        ggY, g2 = _native.sph_double_backward(xyz, grad_Y.contiguous(), v.contiguous(), ctx.l_max,
+        ggY, g2 = _native.sph_double_backward(xyz.contiguous(), grad_Y.contiguous(), v.contiguous(), ctx.l_max,
                                               ctx.normalize, want_grad_grad_Y=want_gg, want_grad_xyz=want_x)
         return ggY, g2, None, None
 
@@ -74,7 +75,7 @@ class _SphE3nn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_Y):
         (xp,) = ctx.saved_tensors
-        return _native.sph_e3nn_vector_jacobian(xp, grad_Y.contiguous(), *ctx.args), None, None, None
+        return _native.sph_e3nn_vector_jacobian(xp.contiguous(), grad_Y.contiguous(), *ctx.args), None, None, None
 
 
 def e3nn_spherical_harmonics(xyz: torch.Tensor, l_max: int, normalize: bool = True,
